@@ -568,20 +568,14 @@ __device__ __forceinline__ double diff_of_products(double a, double b, double c,
 extern "C" __device__ __attribute__((const)) double __ockl_wfred_add_f64(double);
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_max_f32(float);
 extern "C" __device__ __attribute__((const)) float __ockl_wfred_add_f32(float);
+extern "C" __device__ __attribute__((const)) int __ockl_wfred_min_i32(int);
+extern "C" __device__ __attribute__((const)) int __ockl_wfred_max_i32(int);
 namespace sr {
 __device__ __forceinline__ double wave_sum(double v) { return __ockl_wfred_add_f64(v); }
 __device__ __forceinline__ float wave_max(float v) { return __ockl_wfred_max_f32(v); }
 __device__ __forceinline__ float wave_sum_f(float v) { return __ockl_wfred_add_f32(v); }
-__device__ __forceinline__ int wave_min_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o, 64));
-    return v;
-}
-__device__ __forceinline__ int wave_max_i(int v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o, 64));
-    return v;
-}
+__device__ __forceinline__ int wave_min_i(int v) { return __ockl_wfred_min_i32(v); }
+__device__ __forceinline__ int wave_max_i(int v) { return __ockl_wfred_max_i32(v); }
 __device__ __forceinline__ uint32_t lane_prefix(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32),
                                      __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));

@@ -166,26 +166,214 @@ __device__ __forceinline__ float cic_w(float r, int c) {
     return fmaxf(0.0f, 1.0f - fabsf(r - (float)(c - 1)));
 }
 
-// Charge: rho += q w S / dV on the 4 (2D) or 8 (3D) nodes of each particle.
+// A deposit block first finds the box of nodes its particles touch, with cells
+// taken relative to the block's first particle across the periodic boundary (a
+// block whose sorted particles run from the end of one tile row into the next
+// keeps a compact box).  A box above `cap` nodes (particles that have drifted
+// far since the last sort) shrinks, widest axis first, to a window of at most
+// `cap` nodes about the block's mean cell; the particles whose nodes leave the
+// window add to the grid directly.
+template <int WAVES>
+struct DepShared {
+    int red[2][3][WAVES];
+    float bmax[WAVES];
+    int ref[3];
+    float msum[3][WAVES];
+    int mcnt[WAVES];
+};
+struct DepBox {
+    int org[3], ext[3];   // first node (unwrapped) and extent on each axis
+    float bnd;            // the block's largest bound (infinite if one is not finite)
+};
+
+// The box of the block's live particles: I their cells, `bound` >= 0 a bound on
+// each one's contributions; nodes reach from `below` under the smallest cell to
+// `above` over the largest.  U receives the particle's unwrapped cell.  False
+// when no particle is live.  Call with the whole block (thread 0 active).
+template <int DIM, int WAVES>
+__device__ __forceinline__ bool deposit_box(DepShared<WAVES> &sh, const int I[3], bool live,
+                                            float bound, const PicGrid &G, int below, int above,
+                                            int cap, int U[3], DepBox &bx) {
+    if (threadIdx.x == 0)
+        for (int a = 0; a < 3; ++a) sh.ref[a] = I[a];
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        int d = I[a] - sh.ref[a];
+        if (a < DIM) {
+            if (2 * d > G.n[a]) d -= G.n[a];
+            else if (2 * d < -G.n[a]) d += G.n[a];
+        }
+        U[a] = sh.ref[a] + d;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const int lo = wave_min_i(live ? U[a] : 0x3fffffff);
+        const int hi = wave_max_i(live ? U[a] : -0x3fffffff);
+        if (lane == 0) { sh.red[0][a][wave] = lo; sh.red[1][a][wave] = hi; }
+    }
+    {
+        const float b = wave_max(live ? (bound <= 3.0e38f ? bound : __builtin_inff()) : 0.0f);
+        if (lane == 0) sh.bmax[wave] = b;
+    }
+    __syncthreads();
+    bool any = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        bx.org[a] = 0;
+        bx.ext[a] = 1;
+        if (a >= DIM) continue;
+        int lo = sh.red[0][a][0], hi = sh.red[1][a][0];
+        for (int w = 1; w < WAVES; ++w) { lo = min(lo, sh.red[0][a][w]); hi = max(hi, sh.red[1][a][w]); }
+        any = any && hi >= lo;      // no live particle: lo > hi
+        bx.org[a] = lo - below;
+        bx.ext[a] = hi - lo + below + above + 1;
+    }
+    bx.bnd = sh.bmax[0];
+    for (int w = 1; w < WAVES; ++w) bx.bnd = fmaxf(bx.bnd, sh.bmax[w]);
+    if (!any) return false;
+    // volumes in 64 bits: extents can be as large as the grid
+    int64_t vol = (int64_t)bx.ext[0] * bx.ext[1] * bx.ext[2];
+    if (vol <= cap) return true;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const float v = wave_sum_f(live ? (float)(U[a] - sh.ref[a]) : 0.0f);
+        if (lane == 0) sh.msum[a][wave] = v;
+    }
+    const int n_live = (int)__popcll(__ballot(live));
+    if (lane == 0) sh.mcnt[wave] = n_live;
+    __syncthreads();
+    int cnt = 0;
+    for (int w = 0; w < WAVES; ++w) cnt += sh.mcnt[w];
+    for (int it = 0; it < DIM && vol > cap; ++it) {
+        int wide = 0;
+#pragma unroll
+        for (int b = 1; b < DIM; ++b)
+            if (bx.ext[b] > (wide == 0 ? bx.ext[0] : bx.ext[1])) wide = b;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            if (a != wide) continue;
+            const int64_t other = vol / bx.ext[a];
+            const int wdt = (int)min<int64_t>(bx.ext[a], max<int64_t>(4, cap / other));
+            float sum = 0.0f;
+            for (int w = 0; w < WAVES; ++w) sum += sh.msum[a][w];
+            const int c = sh.ref[a] + (int)floorf(sum / (float)max(cnt, 1) + 0.5f);
+            bx.org[a] = min(max(c - wdt / 2, bx.org[a]), bx.org[a] + bx.ext[a] - wdt);
+            bx.ext[a] = wdt;
+            vol = other * wdt;
+        }
+    }
+    return true;
+}
+
+// Grid index of box node l (x fastest), wrapped onto the periodic grid: the
+// nodes lie in [-n/2 - 1, 3n/2 + 1], so two wraps each way reach [0, n) for
+// any n.
 template <int DIM>
-__global__ __launch_bounds__(256) void rho_kernel(sr_particles_f32 P, PicGrid G, float qv,
-                                                  float *__restrict__ rho) {
+__device__ __forceinline__ uint32_t box_node(int l, const DepBox &bx, float inv_e0, float inv_e1,
+                                             const PicGrid &G) {
+    const int r = div_small(l, bx.ext[0], inv_e0), li = l - r * bx.ext[0];
+    const int lk = div_small(r, bx.ext[1], inv_e1), lj = r - lk * bx.ext[1];
+    int i = wrap2(bx.org[0] + li, G.n[0]), j = wrap2(bx.org[1] + lj, G.n[1]);
+    int k = DIM == 3 ? wrap2(bx.org[2] + lk, G.n[2]) : 0;
+    i = min(max(i, 0), G.n[0] - 1);
+    j = min(max(j, 0), G.n[1] - 1);
+    k = min(max(k, 0), G.n[2] - 1);
+    return cell(i, j, k, G);
+}
+
+// Charge: rho += q w S / dV on the 4 (2D) or 8 (3D) nodes of each particle.
+//
+// Added one by one, the contributions of sorted particles are scattered float
+// atomics of one lane each, which is what the deposit took its time for.  The
+// block sums them in its LDS box instead and adds the box's nodes to the grid,
+// consecutive lanes on consecutive nodes.  The sums are exact: a contribution
+// v, the same binary32 product as on the direct path, becomes the integer
+// v 2^(kRhoBits - e) with 2^e above the block's largest |q w / dV|, rounded at
+// 2^(e - kRhoBits - 1); a particle lighter than 2^-18 of the heaviest, where
+// that could lose bits a float would keep, and one whose weight or position is
+// not finite, adds to the grid directly.  At most 2^9 contributions of at most
+// 2^44 units meet on a node, so a sum stays below 2^53 and its conversion back
+// is exact too: a node's block sum is rounded once.  A block most of whose
+// particles lie outside the window (an unsorted ensemble) goes direct.
+constexpr int kRhoThreads = 512;   // particles per block
+constexpr int kRhoWaves = kRhoThreads / 64;
+constexpr int kRhoCells = 6144;    // 48 KB: three blocks per compute unit
+constexpr int kRhoBits = 44;
+
+// v 2^s as a 64-bit integer, for |v 2^s| < 2^51: the sum with 1.5 2^52 leaves
+// the integer, in two's complement, in the low bits of the significand
+__device__ __forceinline__ unsigned long long fixed64(float v, double scale) {
+    const double b = fma((double)v, scale, 6755399441055744.0);
+    return (unsigned long long)(__double_as_longlong(b) - 0x4338000000000000ll);
+}
+
+template <int DIM>
+__global__ __launch_bounds__(kRhoThreads) void rho_kernel(sr_particles_f32 P, PicGrid G, float qv,
+                                                          float *__restrict__ rho) {
+    __shared__ unsigned long long box[kRhoCells];
+    __shared__ DepShared<kRhoWaves> sh;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P.n) return;
-    const uint32_t u = (uint32_t)p;
+    const bool active = p < P.n;
+    const uint32_t u = active ? (uint32_t)p : 0u;
     int I[3] = {0, 0, 0};
     float F[3] = {0.0f, 0.0f, 0.0f};
     for (int a = 0; a < DIM; ++a) locate(ld(P.x[a], u), G.inv_hi[a], G.inv_lo[a], G.n[a], I[a], F[a]);
     const float qw = qv * ld(P.w, u) / G.dV;
-    for (int c = 0; c < (DIM == 3 ? 2 : 1); ++c)
-        for (int b = 0; b < 2; ++b)
-            for (int a = 0; a < 2; ++a) {
-                const float wt = (a ? F[0] : 1.0f - F[0]) * (b ? F[1] : 1.0f - F[1]) *
-                                 (DIM == 3 ? (c ? F[2] : 1.0f - F[2]) : 1.0f);
-                const int i = node(I[0], 1 + a, G.n[0]), j = node(I[1], 1 + b, G.n[1]);
-                const int k = DIM == 3 ? node(I[2], 1 + c, G.n[2]) : 0;
-                unsafeAtomicAdd(&rho[cell(i, j, k, G)], qw * wt);
-            }
+    const auto each = [&](auto &&add) {
+#pragma unroll
+        for (int c = 0; c < (DIM == 3 ? 2 : 1); ++c)
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+#pragma unroll
+                for (int a = 0; a < 2; ++a) {
+                    const float wt = (a ? F[0] : 1.0f - F[0]) * (b ? F[1] : 1.0f - F[1]) *
+                                     (DIM == 3 ? (c ? F[2] : 1.0f - F[2]) : 1.0f);
+                    add(a, b, c, qw * wt);
+                }
+    };
+    bool fin = fabsf(qw) <= 3.0e38f;
+    for (int a = 0; a < DIM; ++a) fin = fin && fabsf(F[a]) <= 1.0f;
+    const bool live = active && fin && qw != 0.0f;
+    int U[3];
+    DepBox bx;
+    const bool any = deposit_box<DIM>(sh, I, live, fabsf(qw), G, 0, 1, kRhoCells, U, bx);
+    bool in_win = live && any && fabsf(qw) * 262144.0f >= bx.bnd;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const int b = U[a] - bx.org[a];
+        in_win = in_win && b >= 0 && b + 1 <= bx.ext[a] - 1;
+    }
+    const bool use_box = 2 * __syncthreads_count(in_win) >= __syncthreads_count(live) && any;
+    in_win = in_win && use_box;
+    if (active && !in_win && (qw != 0.0f || !fin))
+        each([&](int a, int b, int c, float v) {
+            const int i = node(I[0], 1 + a, G.n[0]), j = node(I[1], 1 + b, G.n[1]);
+            const int k = DIM == 3 ? node(I[2], 1 + c, G.n[2]) : 0;
+            unsafeAtomicAdd(&rho[cell(i, j, k, G)], v);
+        });
+    if (!use_box) return;          // the condition is block-wide
+    int e = 0;
+    (void)frexpf(bx.bnd, &e);      // bnd < 2^e
+    const double to_fix = ldexp(1.0, kRhoBits - e), from_fix = ldexp(1.0, e - kRhoBits);
+    const int cells = bx.ext[0] * bx.ext[1] * bx.ext[2];
+    for (int q = threadIdx.x; q < cells; q += kRhoThreads) box[q] = 0;
+    __syncthreads();
+    if (in_win) {
+        const int l0 = (U[0] - bx.org[0]) +
+                       bx.ext[0] * ((U[1] - bx.org[1]) + bx.ext[1] * (DIM == 3 ? U[2] - bx.org[2] : 0));
+        each([&](int a, int b, int c, float v) {
+            atomicAdd(&box[l0 + a + bx.ext[0] * (b + bx.ext[1] * c)], fixed64(v, to_fix));
+        });
+    }
+    __syncthreads();
+    const float inv_e0 = 1.0f / (float)bx.ext[0], inv_e1 = 1.0f / (float)bx.ext[1];
+    for (int q = threadIdx.x; q < cells; q += kRhoThreads) {
+        const long long sum = (long long)box[q];
+        if (sum != 0)
+            unsafeAtomicAdd(&rho[box_node<DIM>(q, bx, inv_e0, inv_e1, G)], (float)((double)sum * from_fix));
+    }
 }
 
 // Esirkepov's current of the move x_old -> x (one lane per particle).  On each
@@ -199,15 +387,9 @@ __global__ __launch_bounds__(256) void rho_kernel(sr_particles_f32 P, PicGrid G,
 // Zero contributions are skipped.  A move of a cell or more sets *status.
 //
 // Sorted particles put the lanes of a block on the same few cells, where
-// global float atomics serialise.  So the block first finds the box of nodes
-// its particles touch, with cells taken relative to the block's first particle
-// across the periodic boundary (a block whose sorted particles run from the end
-// of one tile row into the next keeps a compact box).  If that box fits in LDS
-// (kDepCells cells, three components) the block accumulates there and adds the
-// box's non-zero entries to the grid at the end.  A larger box (particles that
-// have drifted far since the last sort) shrinks to a window of at most
-// kDepCells cells about the block's mean cell, and only the particles whose
-// nodes leave the window add to the grid directly.
+// global float atomics serialise: the block accumulates in its LDS box
+// (deposit_box, kDepCells cells, three components) and adds the box's non-zero
+// entries to the grid at the end.
 //
 // The box holds fixed-point integers, not floats: on gfx950 an LDS float
 // atomic add takes about 40 times as long as an integer one, and it was the
@@ -382,9 +564,7 @@ __global__ __launch_bounds__(kDepThreads) void current_kernel(sr_particles_f32 P
                                                       float *__restrict__ jz,
                                                       uint32_t *__restrict__ status) {
     __shared__ int box[3 * kDepCells];
-    __shared__ int red[2][3][kDepWaves];
-    __shared__ float bmax[kDepWaves];
-    __shared__ int ref[3];
+    __shared__ DepShared<kDepWaves> sh;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = p < P.n;
     const uint32_t u = active ? (uint32_t)p : 0u;
@@ -394,103 +574,24 @@ __global__ __launch_bounds__(kDepThreads) void current_kernel(sr_particles_f32 P
     if (bad) atomicOr(status, SR_W_CFL);
     float *const J[3] = {jx, jy, jz};
 
-    // the cells relative to the block's first particle (always active: the
-    // grid has ceil(n / kDepThreads) blocks), unwrapped across the periodic boundary
-    if (threadIdx.x == 0)
-        for (int a = 0; a < 3; ++a) ref[a] = s.I[a];
-    __syncthreads();
+    // the block's first particle is always active: the grid has
+    // ceil(n / kDepThreads) blocks
     int U[3];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        int d = s.I[a] - ref[a];
-        if (a < DIM) {
-            if (2 * d > G.n[a]) d -= G.n[a];
-            else if (2 * d < -G.n[a]) d += G.n[a];
-        }
-        U[a] = ref[a] + d;
-    }
-
-    // the block's box of nodes [min U - 1, max U + 2] and its largest bound
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        int lo = s.live ? U[a] : 0x3fffffff, hi = s.live ? U[a] : -0x3fffffff;
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = min(lo, __shfl_xor(lo, o, 64));
-            hi = max(hi, __shfl_xor(hi, o, 64));
-        }
-        if (lane == 0) { red[0][a][wave] = lo; red[1][a][wave] = hi; }
-    }
-    {
-        // a non-finite bound (a NaN or infinite weight) counts as infinite
-        float b = s.live ? (s.bound <= 3.0e38f ? s.bound : __builtin_inff()) : 0.0f;
-        for (int o = 32; o > 0; o >>= 1) b = fmaxf(b, __shfl_xor(b, o, 64));
-        if (lane == 0) bmax[wave] = b;
-    }
-    __syncthreads();
-    int org[3], ext[3];
-    bool any = true;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        int lo = red[0][a][0], hi = red[1][a][0];
-        for (int w = 1; w < kDepWaves; ++w) { lo = min(lo, red[0][a][w]); hi = max(hi, red[1][a][w]); }
-        any = any && hi >= lo;      // no live particle: lo > hi
-        if (a < DIM) {
-            org[a] = lo - 1;
-            ext[a] = hi - lo + 4;
-        } else {
-            org[a] = 0;
-            ext[a] = 1;
-        }
-    }
-    if (!any) return;               // no live particle (the condition is block-wide)
-    float bnd = bmax[0];
-    for (int w = 1; w < kDepWaves; ++w) bnd = fmaxf(bnd, bmax[w]);
+    DepBox bx;
+    if (!deposit_box<DIM>(sh, s.I, s.live, s.bound, G, 1, 2, kDepCells, U, bx))
+        return;                     // no live particle (the condition is block-wide)
+    const float bnd = bx.bnd;
     // bnd < 2^e: contributions in units of 2^(e - kDepFracBits).  A
     // non-finite bound, or one so small that 2^(kDepFracBits - e) would not
     // be a finite float, sends the whole block to the float path.
     int e = 0;
     if (bnd > 0.0f) (void)frexpf(bnd, &e);
     const bool fixed = bnd <= 3.0e38f && e >= -100;
-    // A box too large for LDS shrinks, widest axis first, to a window about
-    // the block's mean cell (kept inside the box); the particles whose nodes
-    // leave the window add to the grid directly.  Volumes in 64 bits: extents
-    // can be as large as the grid.
-    int64_t vol = (int64_t)ext[0] * ext[1] * ext[2];
-    if (fixed && vol > kDepCells) {
-        __shared__ float msum[3][kDepWaves];
-        __shared__ int mcnt[kDepWaves];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            float v = s.live ? (float)(U[a] - ref[a]) : 0.0f;
-            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-            if (lane == 0) msum[a][wave] = v;
-        }
-        int live = s.live ? 1 : 0;
-        for (int o = 32; o > 0; o >>= 1) live += __shfl_xor(live, o, 64);
-        if (lane == 0) mcnt[wave] = live;
-        __syncthreads();
-        int cnt = 0;
-        for (int w = 0; w < kDepWaves; ++w) cnt += mcnt[w];
-        for (int it = 0; it < DIM && vol > kDepCells; ++it) {
-            int a = 0;
-            for (int b = 1; b < DIM; ++b)
-                if (ext[b] > ext[a]) a = b;
-            const int64_t other = vol / ext[a];
-            const int wdt = (int)min<int64_t>(ext[a], max<int64_t>(4, kDepCells / other));
-            float sum = 0.0f;
-            for (int w = 0; w < kDepWaves; ++w) sum += msum[a][w];
-            const int c = ref[a] + (int)floorf(sum / (float)max(cnt, 1) + 0.5f);
-            org[a] = min(max(c - wdt / 2, org[a]), org[a] + ext[a] - wdt);
-            ext[a] = wdt;
-            vol = other * wdt;
-        }
-    }
     bool in_win = s.live && fixed;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        const int b = U[a] - 1 + s.o[a] - org[a];
-        in_win = in_win && b >= 0 && b + 2 <= ext[a] - 1;
+        const int b = U[a] - 1 + s.o[a] - bx.org[a];
+        in_win = in_win && b >= 0 && b + 2 <= bx.ext[a] - 1;
     }
     if (s.live && !in_win)
         esirkepov<DIM>(s, [&](int comp, int ci, int cj, int ck, float v) {
@@ -500,36 +601,26 @@ __global__ __launch_bounds__(kDepThreads) void current_kernel(sr_particles_f32 P
         });
     if (!fixed || !(bnd > 0.0f)) return;      // block-wide; bnd = 0: every contribution is zero
     const float to_fix = ldexpf(1.0f, kDepFracBits - e), from_fix = ldexpf(1.0f, e - kDepFracBits);
-    const int cells = ext[0] * ext[1] * ext[2];
+    const int cells = bx.ext[0] * bx.ext[1] * bx.ext[2];
     for (int q = threadIdx.x; q < 3 * cells; q += blockDim.x) box[q] = 0;
     __syncthreads();
     if (in_win) {
-        const int b0 = U[0] - 1 + s.o[0] - org[0], b1 = U[1] - 1 + s.o[1] - org[1];
-        const int b2 = DIM == 3 ? U[2] - 1 + s.o[2] - org[2] : 0;
+        const int b0 = U[0] - 1 + s.o[0] - bx.org[0], b1 = U[1] - 1 + s.o[1] - bx.org[1];
+        const int b2 = DIM == 3 ? U[2] - 1 + s.o[2] - bx.org[2] : 0;
         esirkepov<DIM>(s, [&](int comp, int ci, int cj, int ck, float v) {
-            const int l = (b0 + ci) + ext[0] * ((b1 + cj) + ext[1] * (b2 + ck));
+            const int l = (b0 + ci) + bx.ext[0] * ((b1 + cj) + bx.ext[1] * (b2 + ck));
             atomicAdd(&box[comp * cells + l], __float2int_rn(v * to_fix));
         });
     }
     __syncthreads();
-    const float inv_cells = 1.0f / (float)cells, inv_e0 = 1.0f / (float)ext[0];
-    const float inv_e1 = 1.0f / (float)ext[1];
+    const float inv_cells = 1.0f / (float)cells, inv_e0 = 1.0f / (float)bx.ext[0];
+    const float inv_e1 = 1.0f / (float)bx.ext[1];
     for (int q = threadIdx.x; q < 3 * cells; q += blockDim.x) {
         const int sum = box[q];
         if (sum == 0) continue;
-        const int comp = div_small(q, cells, inv_cells), l = q - comp * cells;
-        const int r = div_small(l, ext[0], inv_e0), li = l - r * ext[0];
-        const int lk = div_small(r, ext[1], inv_e1), lj = r - lk * ext[1];
-        // the box's nodes wrapped onto the periodic grid: they lie in
-        // [-n/2 - 1, 3n/2 + 1], so two wraps each way reach [0, n) for any n
-        int i = org[0] + li, j = org[1] + lj, k = org[2] + lk;
-        i = wrap2(i, G.n[0]);
-        j = wrap2(j, G.n[1]);
-        k = DIM == 3 ? wrap2(k, G.n[2]) : 0;
-        i = min(max(i, 0), G.n[0] - 1);
-        j = min(max(j, 0), G.n[1] - 1);
-        k = min(max(k, 0), G.n[2] - 1);
-        unsafeAtomicAdd(&J[comp][cell(i, j, k, G)], (float)sum * from_fix);
+        const int comp = div_small(q, cells, inv_cells);
+        const uint32_t at = box_node<DIM>(q - comp * cells, bx, inv_e0, inv_e1, G);
+        unsafeAtomicAdd(&J[comp][at], (float)sum * from_fix);
     }
 }
 
@@ -616,10 +707,10 @@ extern "C" int sr_deposit_rho(const sr_particles_f32 *parts, const sr_grid *grid
     if (parts->n == 0) return SR_OK;
     if (!parts->x[0] || !parts->x[1] || (grid->dim == 3 && !parts->x[2]) || !parts->w)
         return SR_E_INVAL;
-    const unsigned nb = (unsigned)((parts->n + 255) / 256);
+    const unsigned nb = (unsigned)((parts->n + kRhoThreads - 1) / kRhoThreads);
     hipStream_t st = (hipStream_t)stream;
-    if (grid->dim == 3) rho_kernel<3><<<nb, 256, 0, st>>>(*parts, G, (float)charge, rho);
-    else rho_kernel<2><<<nb, 256, 0, st>>>(*parts, G, (float)charge, rho);
+    if (grid->dim == 3) rho_kernel<3><<<nb, kRhoThreads, 0, st>>>(*parts, G, (float)charge, rho);
+    else rho_kernel<2><<<nb, kRhoThreads, 0, st>>>(*parts, G, (float)charge, rho);
     SR_HIP_CHECK(hipGetLastError());
     return SR_OK;
 }
