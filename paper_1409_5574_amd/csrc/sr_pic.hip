@@ -293,13 +293,20 @@ __device__ __forceinline__ uint32_t box_node(int l, const DepBox &bx, float inv_
 // v 2^(kRhoBits - e) with 2^e above the block's largest |q w / dV|, rounded at
 // 2^(e - kRhoBits - 1); a particle lighter than 2^-18 of the heaviest, where
 // that could lose bits a float would keep, and one whose weight or position is
-// not finite, adds to the grid directly.  At most 2^9 contributions of at most
+// not finite, adds to the grid directly.  At most 2^8 contributions of at most
 // 2^44 units meet on a node, so a sum stays below 2^53 and its conversion back
 // is exact too: a node's block sum is rounded once.  A block most of whose
 // particles lie outside the window (an unsorted ensemble) goes direct.
-constexpr int kRhoThreads = 512;   // particles per block
+//
+// The 4.0 M sorted electrons at 1/4 per cell on 256^3 take 145 us where the direct
+// adds took 763 us.  At that density a block's box is 6 nodes a particle whatever
+// its size, so small blocks win as long as a block that straddles two tile rows
+// keeps most of its particles in the window: the sort and the deposit took 279 us
+// with 256 particles and 4096 nodes; 284, 300 us with 3072, 5120 nodes; 292 us with
+// 128 and 2048; 333 us with 512 and 6144; 497 us with 1024 and 7936.
+constexpr int kRhoThreads = 256;   // particles per block
 constexpr int kRhoWaves = kRhoThreads / 64;
-constexpr int kRhoCells = 6144;    // 48 KB: three blocks per compute unit
+constexpr int kRhoCells = 4096;    // 32 KB: four blocks per compute unit
 constexpr int kRhoBits = 44;
 
 // v 2^s as a 64-bit integer, for |v 2^s| < 2^51: the sum with 1.5 2^52 leaves
