@@ -256,15 +256,19 @@ __device__ __forceinline__ float trial_x(uint32_t a, float lg, bool lower) {
 // separate loads.  The same values either way, so the same result.
 constexpr int kQHot0 = (-6 * kQPerUnit) - kQJ0;
 constexpr int kQHot = 2 * (kQN - kQHot0);
-template <bool HOT>
-__device__ __forceinline__ float quantum_q_t(uint32_t a, const float4 *__restrict__ qtab,
-                                             const float4 *qhot, float pa, float chi, float &x) {
+// The part of a quantum trial that its word alone sets: x and log2(1/S).
+__device__ __forceinline__ void quantum_draw(uint32_t a, float pa, float &x, float &l2_inv_s) {
     const float rp = (float)((a >> 9) * 2u + 1u) * 0x1p-24f;
     const bool lower = rp <= pa;
     const float lg = __builtin_amdgcn_logf(lower ? rp : 1.0f - rp);
     x = trial_x(a, lg, lower);
     // log2(1/S): lower S = (4/3) R'^{1/4}, upper S = 1 - R'
-    const float l2_inv_s = lower ? -fmaf(0.25f, lg, 0.41503749927884381f) : -lg;
+    l2_inv_s = lower ? -fmaf(0.25f, lg, 0.41503749927884381f) : -lg;
+}
+template <bool HOT>
+__device__ __forceinline__ float quantum_kernel(float x, float l2_inv_s,
+                                                const float4 *__restrict__ qtab,
+                                                const float4 *qhot, float chi) {
     const float delta = 1.5f * chi * x;
     if (!(delta < 1.0f)) return 0.0f;
     const float om = 1.0f - delta;
@@ -294,6 +298,13 @@ __device__ __forceinline__ float quantum_q_t(uint32_t a, const float4 *__restric
     const float q = c * __builtin_amdgcn_exp2f(fmaf(-0.66666666666666667f, t, ya)) -
                     __builtin_amdgcn_exp2f(yb);
     return q * __builtin_amdgcn_exp2f(fmaf(-1.4426950408889634f, xi, l2_inv_s));
+}
+template <bool HOT>
+__device__ __forceinline__ float quantum_q_t(uint32_t a, const float4 *__restrict__ qtab,
+                                             const float4 *qhot, float pa, float chi, float &x) {
+    float l2_inv_s;
+    quantum_draw(a, pa, x, l2_inv_s);
+    return quantum_kernel<HOT>(x, l2_inv_s, qtab, qhot, chi);
 }
 __device__ __forceinline__ float quantum_q(uint32_t a, const float4 *__restrict__ qtab, float pa,
                                            float chi, float &x) {

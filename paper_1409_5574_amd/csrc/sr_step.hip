@@ -157,8 +157,14 @@ __device__ __forceinline__ Pushed<R> push_box(const StepArgs<R> &a, const R pos[
 }
 
 template <typename R>
+__device__ __forceinline__ R gamma_of(const R p[3]) {
+    return sqrt_r<R>((R)1 + p[0] * p[0] + p[1] * p[1] + p[2] * p[2]);
+}
+
+// With g_old = gamma_of(p0) from the caller.
+template <typename R>
 __device__ __forceinline__ Pushed<R> push_fields(const StepArgs<R> &a, const R p0[3], const R E[3],
-                                                 const R B[3]) {
+                                                 const R B[3], R g_old) {
     Pushed<R> o;
     // ---- Boris push (q = -1), keeping the momentum increment d explicitly
     const R h = (R)(-0.5) * a.dt;
@@ -183,8 +189,7 @@ __device__ __forceinline__ Pushed<R> push_fields(const StepArgs<R> &a, const R p
     const R cy = diff_of_products(o.pb[2], d[0], o.pb[0], d[2]);
     const R cz = diff_of_products(o.pb[0], d[1], o.pb[1], d[0]);
     const R c2 = cx * cx + cy * cy + cz * cz;
-    const R g_old = sqrt_r<R>((R)1 + p0[0] * p0[0] + p0[1] * p0[1] + p0[2] * p0[2]);
-    o.g_new = sqrt_r<R>((R)1 + o.pn[0] * o.pn[0] + o.pn[1] * o.pn[1] + o.pn[2] * o.pn[2]);
+    o.g_new = gamma_of<R>(o.pn);
     o.gb = (R)0.5 * (g_old + o.g_new);
     o.pbm = sqrt_r<R>(o.p2);
     // H_eff = 0 when the mean momentum vanishes (no direction of motion)
@@ -192,14 +197,21 @@ __device__ __forceinline__ Pushed<R> push_fields(const StepArgs<R> &a, const R p
     if (ratio > (R)1) ratio = (R)1;
     o.H = o.p2 > (R)0 ? o.gb * ratio * a.inv_dt : (R)0;
     // A push that is not finite gives H_eff = chi = 0: the particle emits
-    // nothing and adds nothing to the ledger; the caller flags it.
-    o.bad = !(isfinite(o.pn[0]) && isfinite(o.pn[1]) && isfinite(o.pn[2]) && isfinite(o.H) &&
-              isfinite(o.gb));
+    // nothing and adds nothing to the ledger; the caller flags it.  A momentum
+    // that is not finite leaves none of g_new and gb finite, and gb and H, both
+    // positive, cannot overflow in their sum (a finite gb is below the root of
+    // the largest number), so one test finds every case.
+    o.bad = !isfinite(o.gb + o.H);
     if (o.bad) o.H = (R)0;
     o.chi = o.bad ? (R)0 : a.hbar_n * o.H * o.gb;
     return o;
 }
 
+template <typename R>
+__device__ __forceinline__ Pushed<R> push_fields(const StepArgs<R> &a, const R p0[3], const R E[3],
+                                                 const R B[3]) {
+    return push_fields<R>(a, p0, E, B, gamma_of<R>(p0));
+}
 
 template <typename R>
 __device__ __forceinline__ R wrap_pos(R v, R L) {
@@ -767,8 +779,6 @@ void push_emit_kernel(const StepArgs<R> a) {
                 // gamma_after - gamma_before without cancellation
                 acc_de += (double)(-wi * removed * (pm_after + pm) * rcp_r<R>(g_after + g_new));
             }
-            if (!(isfinite(pn[0]) && isfinite(pn[1]) && isfinite(pn[2])))
-                flags |= SR_W_NONFINITE;
             st(a.p[0], i, pn[0]); st(a.p[1], i, pn[1]); st(a.p[2], i, pn[2]);
             // ---- position push
             if (a.push_position && a.has_pos) {
@@ -1048,34 +1058,152 @@ __global__ __launch_bounds__(kBlock) void epilogue_second_kernel(
 }
 
 // ---------------------------------------------------------------------------
-// Many steps in one launch in a uniform field (no grid): every particle's state
-// stays in registers across the steps, one wave per block.  Per step: the push
-// and H_eff (eq:effective_H), the K trials of section "Monte Carlo method",
-// photon append into the chunk's segment (shared by all the steps of the
-// launch, each record tagged with its step), recoil and position; each wave
-// writes one partial ledger row per step (partials[s][wave]), which
-// steps_reduce_kernel sums per step in a fixed order.
+// Many steps in one launch in a uniform field (no grid), one block of four waves
+// per chunk of 64 particles.  Per step: the push and H_eff (eq:effective_H), the
+// K trials of section "Monte Carlo method", photon append into the chunk's
+// segment (shared by all the steps of the launch, each record tagged with its
+// step), recoil and position; one partial ledger row per chunk and step
+// (partials[s][chunk]), which steps_reduce_kernel sums per step in a fixed order.
+//
+// A chunk's steps are a serial chain, so the launch takes as long as one step's
+// chain takes, however idle the chip is: 16 384 particles are one wave on each
+// compute unit.  Only the momentum is carried from step to step, so the waves
+// split a step by what needs it:
+//   wave 0     keeps the particles in registers: push, decisions, photons, recoil;
+//   waves 2, 3 the random words and what they alone set, ahead of it: of a
+//              proposal trial the density F/(x S), its logarithm and x;
+//   wave 1     the FP64 ledger sums over the lanes, behind it.
+// They meet at a barrier every T steps and pass records through LDS, two batches
+// of each kind (one written, one read).  The chain is then push, decision and
+// recoil alone, without Philox, table read and wave reductions: about 125 vector
+// instructions at the latency of a lone wave.  1000 steps of 16 384 particles, K = 1:
+// 0.46 ms; as one wave per chunk 1.33 ms (0.73 ms with the waves split but wave 0
+// not yet stripped of what only a photon needs; batches of 4, 8, 16 steps 0.467,
+// 0.456, 0.459 ms; without the ledger wave 0.444 ms, so wave 0 is the chain).
+template <int KMAX>
+constexpr int kStepsBatch = KMAX >= 8 ? 1 : 8 / KMAX;   // T: 33 KB of LDS, four blocks per CU
+
+template <int KMAX>
+struct StepsSmem {
+    static constexpr int T = kStepsBatch<KMAX>;
+    float4 trial[2][T * KMAX][64];
+    float4 led[2][T][64];               // per lane: delta_ph, recoil, chi, |pb|^2
+    float gb[2][T][64];                 // per lane: mean gamma
+    // photons, clamped and dropped energy and condition bits of the steps that
+    // have any (bit t of `rare`)
+    double clamp[2][T], drop[2][T];
+    uint32_t count[2][T], flags[2][T], rare[2];
+};
+
+// What a trial's words alone set, as the record wave 0 reads: the proposal's
+// density q, its logarithm (negative on the lower branch, its opposite on the
+// upper one), x and the decision word; the quantum sampler's x and log2(1/S);
+// the table sampler's word.
+template <int SAMPLER>
+__device__ __forceinline__ float4 trial_record(const TableDev &tab, uint32_t wa, uint32_t wb) {
+    float4 r = make_float4(0.0f, 0.0f, 0.0f, __uint_as_float(wb));
+    if (SAMPLER == SR_SAMPLER_S) {
+        float lg;
+        bool lower;
+        r.x = trial_q(wa, tab.gtab, tab.pa, lg, lower);
+        r.y = lower ? lg : -lg;
+        r.z = trial_x(wa, lg, lower);
+    } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
+        quantum_draw(wa, tab.pa, r.x, r.y);
+    } else {
+        r.x = __uint_as_float(wa);
+    }
+    return r;
+}
+
 template <int KMAX, int SAMPLER>
-__global__ __launch_bounds__(64) void push_emit_steps_kernel(const StepArgs<float> a,
-                                                             int64_t n_steps) {
-    const int lane = threadIdx.x;
-    const uint32_t c = blockIdx.x;                      // chunk = wave = block
+__global__ __launch_bounds__(kBlock) void push_emit_steps_kernel(const StepArgs<float> a,
+                                                                 int64_t n_steps) {
+    constexpr int T = kStepsBatch<KMAX>;
+    __shared__ StepsSmem<KMAX> sm;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t c = blockIdx.x;                      // chunk = block
     const uint32_t s0 = c * (uint32_t)kChunk;
     const uint32_t e0 = min(s0 + (uint32_t)kChunk, (uint32_t)a.n);
     const uint32_t i = s0 + lane;
     const bool active = i < e0;
+    const int K = a.K;
+    const int64_t nb = gridDim.x;
+    const int64_t batches = (n_steps + T - 1) / T;
+    const float wi = active ? ld(a.w, i) : 0.0f;
+    const uint32_t pid = active ? ld(a.id, i) : 0u;
+
+    // every wave takes part in the batches + 2 barriers
+    if (wave >= 2) {
+        // ---- the trials of batch b: pairs of trials of a step, dealt to the two waves
+        constexpr int kPairs = (KMAX + 1) / 2;
+        for (int64_t b = 0; b < batches + 2; ++b) {
+            if (b < batches) {
+#pragma unroll
+                for (int e = 0; e < (T * kPairs + 1) / 2; ++e) {
+                    const int item = 2 * e + (wave - 2);
+                    const int t = item / kPairs, kp = item % kPairs;
+                    if (item >= T * kPairs || 2 * kp >= K) continue;
+                    const uint32_t step = a.step + (uint32_t)(b * T + t);
+                    const uint4 w = philox4x32_10(make_uint4(pid, step, (uint32_t)kp, 0u), a.seed_lo,
+                                                  a.seed_hi);
+                    sm.trial[b & 1][t * KMAX + 2 * kp][lane] = trial_record<SAMPLER>(a.tab, w.x, w.y);
+                    if (2 * kp + 1 < KMAX && 2 * kp + 1 < K)
+                        sm.trial[b & 1][t * KMAX + 2 * kp + 1][lane] =
+                            trial_record<SAMPLER>(a.tab, w.z, w.w);
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    if (wave == 1) {
+        // ---- partial ledger rows of batch b - 2 (fixed-order wave sums)
+        const float sw = wave_sum_f(wi);
+        double *const partials = cold_args<float>().partials;
+        for (int64_t b = 0; b < batches + 2; ++b) {
+            if (b >= 2) {
+                const int h = b & 1;
+                const int left = (int)min<int64_t>(T, n_steps - (b - 2) * T);
+#pragma unroll
+                for (int t = 0; t < T; ++t) {
+                    if (t >= left) break;
+                    const float4 v = sm.led[h][t][lane];
+                    const float gb = sm.gb[h][t][lane];
+                    // Landau-Lifshitz loss of the step (eq:LLformOfRRForce)
+                    const float beta2 = v.w * rcp_r<float>(gb * gb);
+                    const double se = __ballot(v.x != 0.0f) ? wave_sum((double)wi * (double)v.x) : 0.0;
+                    const double sl = wave_sum((double)(wi * a.ll_c * v.z * v.z * beta2));
+                    const double sd = __ballot(v.y != 0.0f) ? wave_sum((double)v.y) : 0.0;
+                    const float cm = wave_max(v.z);
+                    const bool rare = (sm.rare[h] >> t) & 1u;
+                    if (lane == 0) {
+                        double *row = partials + (((b - 2) * T + t) * nb + c) * kPartCols;
+                        row[SR_LED_EMITTED] = se;
+                        row[SR_LED_LL] = sl;
+                        row[SR_LED_RECOIL] = sd;
+                        row[SR_LED_CLAMPED] = rare ? sm.clamp[h][t] : 0.0;
+                        row[SR_LED_DROPPED] = rare ? sm.drop[h][t] : 0.0;
+                        row[SR_LED_PHOTONS] = rare ? (double)sm.count[h][t] : 0.0;
+                        row[SR_LED_WEIGHT] = (double)sw;
+                        row[SR_LED_CHI_MAX] = (double)cm;
+                        row[kPartFlags] = rare ? (double)sm.flags[h][t] : 0.0;
+                        row[kPartFlags + 1] = 0.0;
+                    }
+                }
+            }
+            __syncthreads();
+        }
+        return;
+    }
+
+    // ---- wave 0: the particles
     const uint32_t pp = (uint32_t)a.per_particle;
     const uint32_t seg_base = s0 * pp, seg_cap = (e0 - s0) * pp;
-    const PhotonOut P = cold_args<float>();
-    const int K = a.K;
     const float invK = 1.0f / (float)K;
-    const int64_t nb = gridDim.x;
-
-    float wi = 0.0f, pos[3] = {0.0f, 0.0f, 0.0f}, p[3] = {0.0f, 0.0f, 0.0f};
-    uint32_t pid = 0;
+    float pos[3] = {0.0f, 0.0f, 0.0f}, p[3] = {0.0f, 0.0f, 0.0f};
     if (active) {
-        wi = ld(a.w, i);
-        pid = ld(a.id, i);
         if (a.has_pos) {
             pos[0] = ld(a.x[0], i);
             if (a.x[1]) pos[1] = ld(a.x[1], i);
@@ -1085,144 +1213,149 @@ __global__ __launch_bounds__(64) void push_emit_steps_kernel(const StepArgs<floa
     }
     const float E[3] = {a.g.e0[0], a.g.e0[1], a.g.e0[2]};
     const float B[3] = {a.g.b0[0], a.g.b0[1], a.g.b0[2]};
+    const bool push = a.push_position && a.has_pos;
     uint32_t run_base = 0;
-    for (int64_t si = 0; si < n_steps; ++si) {
-        const uint32_t step = a.step + (uint32_t)si;
-        double acc_emit = 0.0, acc_ll = 0.0, acc_de = 0.0, acc_clamp = 0.0, acc_drop = 0.0;
-        float chif = 0.0f, eps_unit = 0.0f, Hf = 0.0f, dirf[3] = {0.0f, 0.0f, 0.0f};
-        float pn[3] = {p[0], p[1], p[2]}, gb = 1.0f, g_new = 1.0f, p2 = 0.0f, pbm = 0.0f,
-              chi = 0.0f;
-        uint32_t flags = 0;
-        bool bad = false;
-        if (active) {
-            const Pushed<float> q = push_fields<float>(a, p, E, B);
-            pn[0] = q.pn[0]; pn[1] = q.pn[1]; pn[2] = q.pn[2];
-            p2 = q.p2; gb = q.gb; g_new = q.g_new; pbm = q.pbm; chi = q.chi;
-            Hf = q.H;
-            chif = q.chi;
-            bad = q.bad;
-            if (bad) flags |= SR_W_NONFINITE;
-            if (pbm > 0.0f) {
-                const float inv = rcp_r<float>(pbm);
-                dirf[0] = q.pb[0] * inv; dirf[1] = q.pb[1] * inv; dirf[2] = q.pb[2] * inv;
-            }
-            eps_unit = 1.5f * chif * gb;
-        }
-        float delta_ph = 0.0f;
-        uint32_t wave_tot = 0;
-        float2 rr = make_float2(1.0f, 0.0f);
-        if (SAMPLER == SR_SAMPLER_TABLE && active && a.kin_cut) rr = r_lookup(a.tab.r, chif);
-        constexpr bool kProposal = SAMPLER == SR_SAMPLER_S || SAMPLER == SR_SAMPLER_QUANTUM;
-        const float rate = !active ? 0.0f : (kProposal ? a.rate_c * Hf : a.direct_c * Hf * rr.x);
-        const TrialCut cut = trial_cut(SAMPLER == SR_SAMPLER_S && a.kin_cut != 0, chif);
-        uint4 words = make_uint4(0, 0, 0, 0);
-        for (int k = 0; k < KMAX; ++k) {
-            if (k >= K) break;
-            if ((k & 1) == 0)
-                words = philox4x32_10(make_uint4(pid, step, (uint32_t)(k >> 1), 0u), a.seed_lo,
-                                      a.seed_hi);
-            const uint32_t wa = (k & 1) ? words.z : words.x;
-            const uint32_t wb = (k & 1) ? words.w : words.y;
-            float dn = rate, lg = 0.0f, xq = 0.0f;
-            bool lower = true;
-            if (SAMPLER == SR_SAMPLER_S) {
-                dn = rate * trial_q(wa, a.tab.gtab, a.tab.pa, lg, lower);
-                if (trial_is_cut(cut, lg, lower)) dn = 0.0f;
-            } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
-                dn = rate * quantum_q(wa, a.tab.qtab, a.tab.pa, chif, xq);
-            }
-            bool emit;
-            float frac = invK;
-            if (dn >= 1.0f) {
-                emit = true;
-                if (a.dn_policy == SR_DN_WEIGHT) frac = dn * invK;
-            } else {
-                emit = wb < (uint32_t)(dn * 4294967296.0f);
-            }
-            const uint64_t m = __ballot(emit);
-            if (m) {
-                if (emit) {
-                    float x;
-                    if (SAMPLER == SR_SAMPLER_S) {
-                        x = trial_x(wa, lg, lower);
-                    } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
-                        x = xq;
-                    } else {
-                        float lnU, ln1mU;
-                        direct_u(wa, rr, lnU, ln1mU);
-                        x = __builtin_amdgcn_exp2f(t1_log2x(a.tab.t1, lnU, ln1mU));
-                    }
-                    const float eps = eps_unit * x;
-                    const float wph = wi * frac;
-                    delta_ph += frac * eps;
-                    const uint32_t slot = run_base + wave_tot + lane_prefix(m);
-                    if (slot < seg_cap) {
-                        store_photon(P, seg_base + slot, eps, wph, dirf, pos, pid, (uint32_t)k, step);
-                    } else {
-                        acc_drop += (double)wph * (double)eps;
-                        flags |= SR_W_PHOTON_OVERFLOW;
-                    }
-                }
-                wave_tot += (uint32_t)__popcll(m);
-            }
-        }
-        float acc_w = 0.0f;
-        if (active) {
-            acc_emit = (double)wi * (double)delta_ph;
-            const float beta2 = p2 * rcp_r<float>(gb * gb);
-            if (!bad) acc_ll = (double)(wi * a.ll_c * chi * chi * beta2);
-            float delta = 0.0f;
-            if (a.recoil == SR_RECOIL_PHOTON) delta = delta_ph;
-            else if (a.recoil == SR_RECOIL_LL) delta = a.ll_c * chi * chi * pbm * rcp_r<float>(gb);
-            float g_after = g_new;
-            if (delta > 0.0f) {
-                const float pm = sqrt_r<float>(pn[0] * pn[0] + pn[1] * pn[1] + pn[2] * pn[2]);
-                float fac = pm > 0.0f ? 1.0f - delta * rcp_r<float>(pm) : -1.0f;
-                float removed = delta;
-                if (fac < 0.0f) {
-                    acc_clamp = (double)(wi * (delta - pm));
-                    removed = pm;
-                    fac = 0.0f;
-                    flags |= SR_W_RECOIL_CLAMP;
-                }
-                pn[0] *= fac; pn[1] *= fac; pn[2] *= fac;
-                const float pm_after = fac * pm;
-                g_after = sqrt_r<float>(1.0f + pm_after * pm_after);
-                acc_de = (double)(-wi * removed * (pm_after + pm) * rcp_r<float>(g_after + g_new));
-            }
-            if (!(isfinite(pn[0]) && isfinite(pn[1]) && isfinite(pn[2]))) flags |= SR_W_NONFINITE;
-            if (a.push_position && a.has_pos) {
-                const float vdt = a.dt * rcp_r<float>(g_after);
-                pos[0] += vdt * pn[0]; pos[1] += vdt * pn[1]; pos[2] += vdt * pn[2];
-            }
-            p[0] = pn[0]; p[1] = pn[1]; p[2] = pn[2];
-            acc_w = wi;
-        }
-        run_base += wave_tot;
-        // this wave's partial ledger row of the step (fixed-order wave sums)
-        const double se = wave_sum(acc_emit), sl = wave_sum(acc_ll), sd = wave_sum(acc_de);
-        const double sc = __ballot(acc_clamp != 0.0) ? wave_sum(acc_clamp) : 0.0;
-        const double sdr = __ballot(acc_drop != 0.0) ? wave_sum(acc_drop) : 0.0;
-        const float sw = wave_sum_f(acc_w), cm = wave_max(chif);
-        uint32_t wf = 0;
-        if (__ballot(flags != 0)) {
-            wf = flags;
+    float g_old = gamma_of<float>(p);
+    __syncthreads();
+    // Lanes past the chunk's end run along at p = 0 with rate 0 and weight 0.
+    // What a step without photons does not need is kept out of its way: it
+    // branches only on wave-uniform conditions.
+    for (int64_t b = 1; b < batches + 2; ++b) {
+        const int h = (b - 1) & 1;
+        const int left = (int)min<int64_t>(T, n_steps - (b - 1) * T);   // 0 in the last round
+        uint32_t rare = 0;
+        // the records of a step's first trials are read a step ahead
+        constexpr int kAhead = KMAX < 4 ? KMAX : 4;
+        float4 next[kAhead];
 #pragma unroll
-            for (int o = 32; o > 0; o >>= 1) wf |= (uint32_t)__shfl_xor((int)wf, o, 64);
+        for (int k = 0; k < kAhead; ++k) next[k] = sm.trial[h][k][lane];
+        for (int t = 0; t < left; ++t) {
+            float4 rec[kAhead];
+            const int t1 = min(t + 1, T - 1);
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k) {
+                rec[k] = next[k];
+                // whole records: the fields are not to be read where they are used
+                asm volatile("" : "+v"(rec[k].x), "+v"(rec[k].y), "+v"(rec[k].z), "+v"(rec[k].w));
+                next[k] = sm.trial[h][t1 * KMAX + k][lane];
+            }
+            Pushed<float> q = push_fields<float>(a, p, E, B, g_old);
+            const float chif = active ? q.chi : 0.0f;
+            float2 rr = make_float2(1.0f, 0.0f);
+            if (SAMPLER == SR_SAMPLER_TABLE && active && a.kin_cut) rr = r_lookup(a.tab.r, chif);
+            constexpr bool kProposal = SAMPLER == SR_SAMPLER_S || SAMPLER == SR_SAMPLER_QUANTUM;
+            const float rate = !active ? 0.0f : (kProposal ? a.rate_c * q.H : a.direct_c * q.H * rr.x);
+            TrialCut cut{__builtin_inff(), -__builtin_inff()};
+            if (SAMPLER == SR_SAMPLER_S && a.kin_cut != 0) cut = trial_cut(true, chif);
+            float delta_ph = 0.0f, de = 0.0f;
+            double acc_clamp = 0.0, acc_drop = 0.0;
+            uint32_t wave_tot = 0, flags = 0;
+            const auto trial = [&](int k, const float4 r) {
+                const uint32_t wb = __float_as_uint(r.w);
+                float dn = rate;
+                if (SAMPLER == SR_SAMPLER_S) {
+                    dn = rate * r.x;
+                    // trial_is_cut on the record's signed logarithm
+                    if (r.y > (r.y < 0.0f ? cut.lo : -cut.hi)) dn = 0.0f;
+                } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
+                    dn = rate * quantum_kernel<false>(r.x, r.y, a.tab.qtab, nullptr, chif);
+                }
+                const bool sure = dn >= 1.0f;
+                const bool emit = sure || wb < (uint32_t)((dn < 1.0f ? dn : 0.0f) * 4294967296.0f);
+                const uint64_t m = __ballot(emit);
+                if (m) {
+                    if (emit) {
+                        const float frac = sure && a.dn_policy == SR_DN_WEIGHT ? dn * invK : invK;
+                        float x = SAMPLER == SR_SAMPLER_S ? r.z : r.x;
+                        if (SAMPLER == SR_SAMPLER_TABLE) {
+                            float lnU, ln1mU;
+                            direct_u(__float_as_uint(r.x), rr, lnU, ln1mU);
+                            x = __builtin_amdgcn_exp2f(t1_log2x(a.tab.t1, lnU, ln1mU));
+                        }
+                        const float eps = 1.5f * chif * q.gb * x;
+                        const float wph = wi * frac;
+                        delta_ph += frac * eps;
+                        const uint32_t slot = run_base + wave_tot + lane_prefix(m);
+                        if (slot < seg_cap) {
+                            float dirf[3] = {0.0f, 0.0f, 0.0f};
+                            if (q.pbm > 0.0f) {
+                                const float inv = rcp_r<float>(q.pbm);
+                                dirf[0] = q.pb[0] * inv; dirf[1] = q.pb[1] * inv; dirf[2] = q.pb[2] * inv;
+                            }
+                            store_photon(cold_args<float>(), seg_base + slot, eps, wph, dirf, pos, pid,
+                                         (uint32_t)k, a.step + (uint32_t)((b - 1) * T + t));
+                        } else {
+                            acc_drop += (double)wph * (double)eps;
+                            flags |= SR_W_PHOTON_OVERFLOW;
+                        }
+                    }
+                    wave_tot += (uint32_t)__popcll(m);
+                }
+            };
+#pragma unroll
+            for (int k = 0; k < kAhead; ++k)
+                if (k < K) trial(k, rec[k]);
+            for (int k = kAhead; k < KMAX && k < K; ++k) trial(k, sm.trial[h][t * KMAX + k][lane]);
+
+            const bool any_bad = __ballot(q.bad) != 0;
+            if (any_bad && q.bad) {
+                // no entry in the ledger (chi is 0 already)
+                q.p2 = 0.0f;
+                q.gb = 1.0f;
+                if (active) flags |= SR_W_NONFINITE;
+            }
+            // ---- recoil along the post-push momentum
+            float g_after = q.g_new;
+            g_old = q.g_new;
+            if (a.recoil == SR_RECOIL_LL || (a.recoil == SR_RECOIL_PHOTON && wave_tot)) {
+                const float delta = a.recoil == SR_RECOIL_LL
+                                        ? a.ll_c * chif * chif * q.pbm * rcp_r<float>(q.gb) : delta_ph;
+                if (delta > 0.0f) {
+                    const float pm = sqrt_r<float>(
+                        fmaf(q.pn[2], q.pn[2], fmaf(q.pn[0], q.pn[0], q.pn[1] * q.pn[1])));
+                    float fac = pm > 0.0f ? 1.0f - delta * rcp_r<float>(pm) : -1.0f;
+                    float removed = delta;
+                    if (fac < 0.0f) {
+                        acc_clamp = (double)(wi * (delta - pm));
+                        removed = pm;
+                        fac = 0.0f;
+                        flags |= SR_W_RECOIL_CLAMP;
+                    }
+                    q.pn[0] *= fac; q.pn[1] *= fac; q.pn[2] *= fac;
+                    const float pm_after = fac * pm;
+                    g_after = sqrt_r<float>(1.0f + pm_after * pm_after);
+                    de = -wi * removed * (pm_after + pm) * rcp_r<float>(g_after + q.g_new);
+                    g_old = gamma_of<float>(q.pn);
+                }
+            }
+            if (push) {
+                const float vdt = a.dt * rcp_r<float>(g_after);
+                pos[0] += vdt * q.pn[0]; pos[1] += vdt * q.pn[1]; pos[2] += vdt * q.pn[2];
+            }
+            p[0] = q.pn[0]; p[1] = q.pn[1]; p[2] = q.pn[2];
+            sm.led[h][t][lane] = make_float4(delta_ph, de, chif, q.p2);
+            sm.gb[h][t][lane] = q.gb;
+            if (wave_tot || any_bad || a.recoil == SR_RECOIL_LL) {
+                run_base += wave_tot;
+                rare |= 1u << t;
+                const double sc = __ballot(acc_clamp != 0.0) ? wave_sum(acc_clamp) : 0.0;
+                const double sdr = __ballot(acc_drop != 0.0) ? wave_sum(acc_drop) : 0.0;
+                uint32_t wf = 0;
+                if (__ballot(flags != 0)) {
+                    wf = flags;
+#pragma unroll
+                    for (int o = 32; o > 0; o >>= 1) wf |= (uint32_t)__shfl_xor((int)wf, o, 64);
+                }
+                if (lane == 0) {
+                    sm.clamp[h][t] = sc;
+                    sm.drop[h][t] = sdr;
+                    sm.count[h][t] = wave_tot;
+                    sm.flags[h][t] = wf;
+                }
+            }
         }
-        if (lane == 0) {
-            double *row = P.partials + (si * nb + c) * kPartCols;
-            row[SR_LED_EMITTED] = se;
-            row[SR_LED_LL] = sl;
-            row[SR_LED_RECOIL] = sd;
-            row[SR_LED_CLAMPED] = sc;
-            row[SR_LED_DROPPED] = sdr;
-            row[SR_LED_PHOTONS] = (double)wave_tot;
-            row[SR_LED_WEIGHT] = (double)sw;
-            row[SR_LED_CHI_MAX] = (double)cm;
-            row[kPartFlags] = (double)wf;
-            row[kPartFlags + 1] = 0.0;
-        }
+        if (lane == 0) sm.rare[h] = rare;
+        __syncthreads();
     }
     if (active) {
         st(a.p[0], i, p[0]); st(a.p[1], i, p[1]); st(a.p[2], i, p[2]);
@@ -1232,7 +1365,7 @@ __global__ __launch_bounds__(64) void push_emit_steps_kernel(const StepArgs<floa
             if (a.x[2]) st(a.x[2], i, pos[2]);
         }
     }
-    if (lane == 0) P.seg_count[c] = run_base;
+    if (lane == 0) cold_args<float>().seg_count[c] = run_base;
 }
 
 // Ledger row s of a multi-step launch: the nb partial rows of step s, summed in
@@ -1465,7 +1598,7 @@ int launch_steps(sr_particles_f32 *parts, const sr_grid *grid, double dt, uint64
     const int K = prm->n_samples;
     const int KM = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : K <= 8 ? 8 : 16;
     const unsigned nb = (unsigned)n_chunks;
-#define SR_STEPS(KMV, SMP) push_emit_steps_kernel<KMV, SMP><<<nb, 64, 0, st>>>(a, n_steps)
+#define SR_STEPS(KMV, SMP) push_emit_steps_kernel<KMV, SMP><<<nb, kBlock, 0, st>>>(a, n_steps)
 #define SR_STEPS_K(SMP)                      \
     switch (KM) {                            \
         case 1: SR_STEPS(1, SMP); break;     \
