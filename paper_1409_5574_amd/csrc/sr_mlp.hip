@@ -11,20 +11,21 @@ namespace sr {
 namespace {
 
 // ------------------------------------------------------------------ inference
-__global__ __launch_bounds__(kBlock) void mlp_forward_kernel(const __bf16 *__restrict__ params,
-                                                             const float2 *__restrict__ feats,
-                                                             float *__restrict__ out, int64_t M) {
-    __shared__ MlpSmem s;
-    __shared__ alignas(16) __bf16 tbuf[kWaves][2 * 16 * kH];
-    mlp_load(s, params, threadIdx.x, blockDim.x);
+constexpr int kForwardBlocks = 512;   // two blocks per CU: the weights stay in registers
+__global__ __launch_bounds__(kBlock, 2) void mlp_forward_kernel(const __bf16 *__restrict__ params,
+                                                                const float2 *__restrict__ feats,
+                                                                float *__restrict__ out, int64_t M) {
+    __shared__ MlpFrag sh;
+    mlp_load_frag(sh, params, threadIdx.x, blockDim.x);
     __syncthreads();
+    const MlpRegs s(sh);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15;
     for (int64_t tile = (int64_t)blockIdx.x * kWaves + wave; tile * 16 < M;
          tile += (int64_t)gridDim.x * kWaves) {
         const int64_t idx = tile * 16 + r;
         const bool valid = idx < M;
         const float2 f = valid ? feats[idx] : make_float2(0.f, 0.f);
-        const float y = mlp_tile16(s, tbuf[wave], f.x, f.y);
+        const float y = mlp_tile16(s, f.x, f.y);
         if (valid && lane < 16) out[idx] = y;
     }
 }
@@ -485,7 +486,7 @@ extern "C" int sr_mlp_forward(const void *params, const float *feats, float *out
     if (M == 0) return SR_OK;
     int64_t tiles = (M + 15) / 16;
     int64_t blocks = (tiles + kWaves - 1) / kWaves;
-    if (blocks > 4096) blocks = 4096;
+    if (blocks > kForwardBlocks) blocks = kForwardBlocks;
     mlp_forward_kernel<<<(unsigned)blocks, kBlock, 0, (hipStream_t)stream>>>(
         (const __bf16 *)params, (const float2 *)feats, out, M);
     SR_HIP_CHECK(hipGetLastError());

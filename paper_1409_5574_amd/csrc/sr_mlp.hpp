@@ -3,9 +3,9 @@
 // Network: features (f0, f1) -> 64 -> SiLU -> 64 -> SiLU -> 64 -> SiLU -> 1,
 // output log2 x.  f0 = (log10 chi + 1)/3, f1 = logit(u)/16.  Parameters are one flat
 // bfloat16 vector: W1[64][2], b1[64], W2[64][64], b2[64], W3[64][64], b3[64],
-// W4[64], b4 (8577 values).  The two 64x64 layers run on the matrix cores
-// (v_mfma_f32_16x16x32_bf16: bfloat16 inputs, FP32 accumulation) over tiles of
-// 16 samples per wave; the 2->64 and 64->1 layers are FP32 vector code.
+// W4[64], b4 (8577 values).  Inference runs the first three layers on the matrix
+// cores (v_mfma_f32_16x16x32_bf16: bfloat16 inputs, FP32 accumulation) over tiles
+// of 16 samples per wave; the 64->1 layer is FP32 vector code.
 #pragma once
 
 #include "sr_common.hpp"
@@ -75,14 +75,247 @@ __device__ __forceinline__ f32x4 mfma_split(const Split8 &a, const bf16x8 &b, f3
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a.lo, b, acc, 0, 0, 0);
 }
 
-// Forward pass of 16 samples by one wave.  Lane l works on sample r = l & 15
-// (the four lanes sharing r pass the same features); g = l >> 4.  tb is a
-// per-wave LDS buffer of 2 x 16 x 64 bfloat16.  Returns log2 x of sample r.
+// The same with the activations as the B operand.
+__device__ __forceinline__ f32x4 mfma_split(const bf16x8 &w, const Split8 &a, f32x4 acc) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a.hi, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a.lo, acc, 0, 0, 0);
+}
+
+// ---------------------------------------------------------------- inference
+// A tile is 16 samples.  Each layer is computed transposed, D = W H^T: the weights
+// are the A operand and the activations the B operand, so that a lane keeps one
+// sample (r = lane & 15) through the whole network.  Matrix-core layout (16x16x32):
+// A[i][k] sits in lane i + 16 (k/8) as element k mod 8, B[k][j] in lane j + 16 (k/8),
+// D[i][j] in lane j + 16 (i/4) as element i mod 4.  Lane (r, g = lane >> 4) thus gets
+// the outputs 16 n + 4 g + q of sample r (n = 0..3 the tile of outputs, q = 0..3),
+// and what it needs of the next layer's input are eight values of sample r per
+// block of 32.  The order in which a layer's inputs are numbered is free as long as
+// weights and activations agree: with slot (kb, g, e) standing for input
+// 16 (2 kb + e/4) + 4 g + e mod 4, the lane's outputs are its next inputs, and no
+// layer goes through LDS.  (With the layers the other way round the outputs of a
+// layer were turned over through 4 KB of LDS per wave.)
 //
-// Matrix-core operand layout (16x16x32): A[i][k] sits in lane i + 16 (k/8 mod 4)
-// as element k mod 8 of K-block k/32; B[k][j] likewise in lane j + 16 (...); the
-// 16x16 FP32 result D[i][j] sits in lane j + 16 (i/4), element i mod 4.
-__device__ __forceinline__ float mlp_tile16(const MlpSmem &s, __bf16 *tb, float f0, float f1) {
+// What bounds it is the activations: 192 SiLU a sample, an exponential and a
+// reciprocal each at a quarter of the vector rate.  So the network runs in units of
+// log2 e: with z' = z log2 e, silu(z) log2 e = z' / (1 + 2^-z'), and the factor
+// passes through the layers (biases are scaled, the last layer's weights by ln 2),
+// which leaves four instructions an activation; and the low half of a split
+// activation comes from one dot product, v - 1 hi, without unpacking hi.  3.1 M samples
+// take 203 us (306 vector instructions a tile, 96 of them transcendental: 192 us of
+// issue), 240 us with layers turned over in LDS and natural units (494 a tile).
+// The first layer's inputs are each split in three bfloat16 (24 bits, exact), and
+// its bias enters as three more inputs that hold log2 e.
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+
+// The network's operands, one 16-byte fragment per lane, tile and block: conflict-free
+// reads in LDS, and registers where a wave runs many tiles.
+struct alignas(16) MlpFrag {
+    bf16x8 W1[4][64];
+    bf16x8 W2[4][2][64], W3[4][2][64];
+    f32x4 b2[16], b3[16], W4[16];   // [4 n + g]: b2, b3 times log2 e, W4 times ln 2
+    float b4;
+    __device__ __forceinline__ bf16x8 w1(int n, int l) const { return W1[n][l]; }
+    __device__ __forceinline__ bf16x8 w2(int n, int kb, int l) const { return W2[n][kb][l]; }
+    __device__ __forceinline__ bf16x8 w3(int n, int kb, int l) const { return W3[n][kb][l]; }
+    __device__ __forceinline__ f32x4 bias2(int n, int g) const { return b2[4 * n + g]; }
+    __device__ __forceinline__ f32x4 bias3(int n, int g) const { return b3[4 * n + g]; }
+    __device__ __forceinline__ f32x4 weight4(int n, int g) const { return W4[4 * n + g]; }
+    __device__ __forceinline__ float bias4() const { return b4; }
+};
+
+// One lane's fragments in registers.
+struct MlpRegs {
+    bf16x8 f1[4], f2[4][2], f3[4][2];
+    f32x4 c2[4], c3[4], c4[4];
+    float b4;
+    __device__ __forceinline__ explicit MlpRegs(const MlpFrag &s) {
+        const int l = threadIdx.x & 63, g = l >> 4;
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            f1[n] = s.W1[n][l];
+            f2[n][0] = s.W2[n][0][l]; f2[n][1] = s.W2[n][1][l];
+            f3[n][0] = s.W3[n][0][l]; f3[n][1] = s.W3[n][1][l];
+            c2[n] = s.b2[4 * n + g]; c3[n] = s.b3[4 * n + g]; c4[n] = s.W4[4 * n + g];
+        }
+        b4 = s.b4;
+    }
+    __device__ __forceinline__ bf16x8 w1(int n, int) const { return f1[n]; }
+    __device__ __forceinline__ bf16x8 w2(int n, int kb, int) const { return f2[n][kb]; }
+    __device__ __forceinline__ bf16x8 w3(int n, int kb, int) const { return f3[n][kb]; }
+    __device__ __forceinline__ f32x4 bias2(int n, int) const { return c2[n]; }
+    __device__ __forceinline__ f32x4 bias3(int n, int) const { return c3[n]; }
+    __device__ __forceinline__ f32x4 weight4(int n, int) const { return c4[n]; }
+    __device__ __forceinline__ float bias4() const { return b4; }
+};
+
+// 2^-z' of -z' > 128 is infinite and its reciprocal 0
+__device__ __forceinline__ float silu_log2e(float z) {
+    return z * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-z));
+}
+
+__device__ __forceinline__ void mlp_load_frag(MlpFrag &s, const __bf16 *__restrict__ p, int tid,
+                                              int nt) {
+    const __bf16 zero = (__bf16)0.0f;
+    for (int i = tid; i < 4 * 64; i += nt) {
+        const int row = 16 * (i >> 6) + (i & 15), g = (i >> 4) & 3;
+        bf16x8 f = {zero, zero, zero, zero, zero, zero, zero, zero};
+        if (g == 0) {
+            const __bf16 w0 = p[kOffW1 + 2 * row], w1 = p[kOffW1 + 2 * row + 1];
+            f = (bf16x8){w0, w0, w0, w1, w1, w1, zero, zero};
+        } else if (g == 1) {
+            const __bf16 b = p[kOffB1 + row];
+            f = (bf16x8){b, b, b, zero, zero, zero, zero, zero};
+        }
+        s.W1[i >> 6][i & 63] = f;
+    }
+    for (int i = tid; i < 2 * 8 * 64; i += nt) {
+        const int layer = i >> 9, n = (i >> 7) & 3, kb = (i >> 6) & 1, lane = i & 63;
+        const __bf16 *w = p + (layer ? kOffW3 : kOffW2) + (16 * n + (lane & 15)) * kH + 32 * kb +
+                          4 * (lane >> 4);
+        const bf16x4 lo = *(const bf16x4 *)w, hi = *(const bf16x4 *)(w + 16);
+        (layer ? s.W3 : s.W2)[n][kb][lane] = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+    for (int i = tid; i < kH; i += nt) {
+        ((float *)s.b2)[i] = (float)p[kOffB2 + i] * 1.4426950408889634f;
+        ((float *)s.b3)[i] = (float)p[kOffB3 + i] * 1.4426950408889634f;
+        ((float *)s.W4)[i] = (float)p[kOffW4 + i] * 0.69314718055994531f;
+    }
+    if (tid == 0) s.b4 = (float)p[kOffB4];
+}
+
+// The B operand of a layer from the lane's outputs of the one before: silu, then
+// the two bfloat16 of each activation.
+__device__ __forceinline__ void mlp_activate(const f32x4 z[4], Split8 a[2]) {
+    // (-1, 0) and (0, -1), from registers: as an inline constant the instruction
+    // takes -1.0 for a binary32 one, whose bits are the second of these
+    uint32_t lo_bits = 0x0000BF80u, hi_bits = 0xBF800000u;
+    asm("" : "+v"(lo_bits), "+v"(hi_bits));
+    const bf16x2 minus_lo = __builtin_bit_cast(bf16x2, lo_bits);
+    const bf16x2 minus_hi = __builtin_bit_cast(bf16x2, hi_bits);
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+            const float v0 = silu_log2e(z[n][q]), v1 = silu_log2e(z[n][q + 1]);
+            bf16x2 h;
+            h[0] = (__bf16)v0;
+            h[1] = (__bf16)v1;
+            const int e = 4 * (n & 1) + q;
+            a[n >> 1].hi[e] = h[0];
+            a[n >> 1].hi[e + 1] = h[1];
+            a[n >> 1].lo[e] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(h, minus_lo, v0, false);
+            a[n >> 1].lo[e + 1] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(h, minus_hi, v1, false);
+        }
+}
+
+// Three bfloat16 whose sum is v (24 significant bits).
+__device__ __forceinline__ void split3(float v, __bf16 &h, __bf16 &m, __bf16 &l) {
+    h = (__bf16)v;
+    const float r = v - (float)h;
+    m = (__bf16)r;
+    l = (__bf16)(r - (float)m);
+}
+
+// log2 x of the tile's sample r = lane & 15, whose features (f0, f1) the four lanes
+// that share r pass; s: the fragments in LDS, or a MlpRegs copy of the lane's.
+template <typename FRAG>
+__device__ __forceinline__ float mlp_tile16(const FRAG &s, float f0, float f1) {
+    const int l = threadIdx.x & 63, g = l >> 4;
+    bf16x8 x;
+    {
+        __bf16 a0, a1, a2, c0, c1, c2;
+        split3(f0 * 1.4426950408889634f, a0, a1, a2);
+        split3(f1 * 1.4426950408889634f, c0, c1, c2);
+        // lanes of group 1 hold log2 e for the bias; the others' weights are zero
+        const __bf16 e0 = (__bf16)1.4453125f, e1 = (__bf16)-0.00262451171875f,
+                     e2 = (__bf16)7.063150405883789e-06f;
+        const bool bias = g == 1;
+        x = (bf16x8){bias ? e0 : a0, bias ? e1 : a1, bias ? e2 : a2, c0, c1, c2, c2, c2};
+    }
+    f32x4 z[4];
+#pragma unroll
+    for (int n = 0; n < 4; ++n)
+        z[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s.w1(n, l), x, (f32x4){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    Split8 a[2];
+    mlp_activate(z, a);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        z[n] = s.bias2(n, g);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) z[n] = mfma_split(s.w2(n, kb, l), a[kb], z[n]);
+    }
+    mlp_activate(z, a);
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        z[n] = s.bias3(n, g);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) z[n] = mfma_split(s.w3(n, kb, l), a[kb], z[n]);
+    }
+    float y = 0.0f;
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+        const f32x4 w = s.weight4(n, g);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y = fmaf(w[q], silu_log2e(z[n][q]), y);
+    }
+    y += __shfl_xor(y, 16, 64);
+    y += __shfl_xor(y, 32, 64);
+    return y + s.bias4();
+}
+
+// ---------------------------------------------------------------- in the step
+// The network inside the emission step, one tile at a time between the trials of a
+// wave, with the weights in LDS (the step has no registers for them).  Its x feeds
+// the recoil, so it keeps the arithmetic the step has always had: FP32 first and
+// last layers, natural order of the sums.  The middle layers are laid out so that
+// nothing goes through LDS: layer 2 is transposed (weights as the A operand) with
+// its outputs numbered so that lane (r, g) gets the values 32 kb + 8 g + e of sample
+// r, which is the A operand of layer 3 as it stands; layer 3 has the activations as
+// the A operand, so the sum over its outputs runs over the 16 lanes of a row.
+// 2^20 electrons, K = 8, half of the chi bins on the network: a step takes 152 us,
+// 168 us with both middle layers turned over through LDS (and the same bits).
+struct alignas(16) MlpStepSmem {
+    bf16x8 W2[4][2][64], W3[4][2][64];   // one 16-byte fragment per lane
+    float W1[2 * kH];
+    float b1[kH], b2[kH], b3[kH], W4[kH];
+    float b4;
+};
+
+__device__ __forceinline__ void mlp_load_step(MlpStepSmem &s, const __bf16 *__restrict__ p, int tid,
+                                              int nt) {
+    for (int i = tid; i < 2 * 8 * 64; i += nt) {
+        const int layer = i >> 9, n = (i >> 7) & 3, kb = (i >> 6) & 1, lane = i & 63, r = lane & 15;
+        const int row = layer ? 16 * n + r : 32 * (n >> 1) + 8 * (r >> 2) + 4 * (n & 1) + (r & 3);
+        (layer ? s.W3 : s.W2)[n][kb][lane] =
+            *(const bf16x8 *)(p + (layer ? kOffW3 : kOffW2) + row * kH + 32 * kb + 8 * (lane >> 4));
+    }
+    for (int i = tid; i < 2 * kH; i += nt) s.W1[i] = (float)p[kOffW1 + i];
+    for (int i = tid; i < kH; i += nt) {
+        s.b1[i] = (float)p[kOffB1 + i];
+        s.b2[i] = (float)p[kOffB2 + i];
+        s.b3[i] = (float)p[kOffB3 + i];
+        s.W4[i] = (float)p[kOffW4 + i];
+    }
+    if (tid == 0) s.b4 = (float)p[kOffB4];
+}
+
+// v plus the same of the lane a row rotation or quad permutation away
+template <int CTRL>
+__device__ __forceinline__ float add_dpp(float v) {
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL,
+                                                                     0xF, 0xF, true));
+}
+// Sum over the 16 lanes of a row, as the butterfly over lane bits 3, 2, 1, 0 gives it:
+// rotations by 8 and 4 (after the first, lanes 8 apart agree) and quad permutations.
+__device__ __forceinline__ float row_sum(float v) {
+    v = add_dpp<0x128>(v);   // row_ror:8
+    v = add_dpp<0x124>(v);   // row_ror:4
+    v = add_dpp<0x4E>(v);    // quad_perm:[2,3,0,1]
+    return add_dpp<0xB1>(v); // quad_perm:[1,0,3,2]
+}
+
+// log2 x of sample r = lane & 15 (the four lanes sharing r pass the same features).
+__device__ __forceinline__ float mlp_tile16_step(const MlpStepSmem &s, float f0, float f1) {
     const int l = threadIdx.x & 63, r = l & 15, g = l >> 4;
     Split8 a[2];
 #pragma unroll
@@ -92,43 +325,24 @@ __device__ __forceinline__ float mlp_tile16(const MlpSmem &s, __bf16 *tb, float 
             const int k = 32 * kb + 8 * g + e;
             split_set(a[kb], e, silu(fmaf(s.W1[2 * k], f0, fmaf(s.W1[2 * k + 1], f1, s.b1[k]))));
         }
-    // layer 2
     f32x4 acc[4];
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
         acc[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const bf16x8 b = *(const bf16x8 *)&s.W2[(16 * n + r) * kH + 32 * kb + 8 * g];
-            acc[n] = mfma_split(a[kb], b, acc[n]);
-        }
+        for (int kb = 0; kb < 2; ++kb) acc[n] = mfma_split(s.W2[n][kb][l], a[kb], acc[n]);
     }
-    // to the A layout through LDS: hi part in tb[0..1023], lo part in tb[1024..2047]
 #pragma unroll
     for (int n = 0; n < 4; ++n)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float v = silu(acc[n][q] + s.b2[16 * n + r]);
-            const __bf16 h = (__bf16)v;
-            tb[(4 * g + q) * kH + 16 * n + r] = h;
-            tb[16 * kH + (4 * g + q) * kH + 16 * n + r] = (__bf16)(v - (float)h);
-        }
-    wave_lds_sync();
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb) {
-        a[kb].hi = *(const bf16x8 *)&tb[r * kH + 32 * kb + 8 * g];
-        a[kb].lo = *(const bf16x8 *)&tb[16 * kH + r * kH + 32 * kb + 8 * g];
-    }
-    wave_lds_sync();
-    // layer 3
+        for (int q = 0; q < 4; ++q)
+            split_set(a[n >> 1], 4 * (n & 1) + q,
+                      silu(acc[n][q] + s.b2[32 * (n >> 1) + 8 * g + 4 * (n & 1) + q]));
 #pragma unroll
     for (int n = 0; n < 4; ++n) {
         acc[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) {
-            const bf16x8 b = *(const bf16x8 *)&s.W3[(16 * n + r) * kH + 32 * kb + 8 * g];
-            acc[n] = mfma_split(a[kb], b, acc[n]);
-        }
+        for (int kb = 0; kb < 2; ++kb) acc[n] = mfma_split(a[kb], s.W3[n][kb][l], acc[n]);
     }
     // layer 4: per row partial dot products, summed over the 16 lanes of the group
     float sq[4] = {0.f, 0.f, 0.f, 0.f};
@@ -139,9 +353,7 @@ __device__ __forceinline__ float mlp_tile16(const MlpSmem &s, __bf16 *tb, float 
         for (int q = 0; q < 4; ++q) sq[q] = fmaf(w4, silu(acc[n][q] + b3), sq[q]);
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) sq[q] += __shfl_xor(sq[q], o, 64);
+    for (int q = 0; q < 4; ++q) sq[q] = row_sum(sq[q]);
     // sample r's output lives in group r/4, element r mod 4
     float y = 0.f;
 #pragma unroll

@@ -279,16 +279,15 @@ struct LedgerSmem {
 constexpr int kPartCols = SR_LEDGER_COLS + 2;
 constexpr int kPartFlags = SR_LEDGER_COLS;
 
-// LDS of the kernel.  With the MLP sampler: the network, and per wave the
-// compacted inputs of the emitted trials and a 16x64 transpose buffer, which
-// the ledger reduction reuses after the last round.
+// LDS of the kernel.  With the MLP sampler: the network and, per wave, the
+// compacted inputs of the emitted trials, which the ledger reduction reuses
+// after the last round.
 template <int KMAX, int SAMPLER, bool BOX = false>
 struct alignas(16) StepSmem {
     union {
         struct {
-            MlpSmem m;
+            MlpStepSmem m;
             alignas(16) float2 io[kWaves][64 * KMAX];
-            alignas(16) __bf16 tb[kWaves][2 * 16 * kH];
         };
         LedgerSmem led;
     };
@@ -411,9 +410,12 @@ __device__ __forceinline__ bool load_field_box(const StepArgs<R> &a, BoxSmem &sm
 
 // Occupancy target: the FP32 3D kernels with 4 to 8 trials sit a couple of
 // VGPRs above the 96 that five waves per SIMD allow; asking for five costs no
-// spills and gives them a fifth wave.
+// spills and gives them a fifth wave.  The learned sampler's come to 156 with 8
+// trials; four waves (128 VGPRs, and the 34 KB of LDS allow four blocks per CU)
+// took the step of 2^20 electrons from 159 to 152 us.
 template <typename R, int DIM, int KMAX, int SAMPLER>
 constexpr int step_waves_per_eu() {
+    if (sizeof(R) == 4 && SAMPLER == SR_SAMPLER_MLP && KMAX >= 4 && KMAX <= 8) return 4;
     return (sizeof(R) == 4 && DIM == 3 && KMAX >= 4 && KMAX <= 8 && SAMPLER != SR_SAMPLER_MLP) ? 5
                                                                                               : 1;
 }
@@ -436,7 +438,7 @@ void push_emit_kernel(const StepArgs<R> a) {
         bool any_net = false;
         for (int b = 0; b < kMlpFallbackBins; ++b) any_net |= a.mlp_fallback[b] == 0;
         if (any_net) {
-            mlp_load(sm.m, a.mlp, tid, kBlock);
+            mlp_load_step(sm.m, a.mlp, tid, kBlock);
             __syncthreads();
         }
     }
@@ -721,7 +723,7 @@ void push_emit_kernel(const StepArgs<R> a) {
                 for (uint32_t t0 = 0; t0 < net_tot; t0 += 16) {
                     const uint32_t e = t0 + r16;
                     const float2 f = e < net_tot ? io[e] : make_float2(0.0f, 0.0f);
-                    const float y = mlp_tile16(sm.m, sm.tb[wave], f.x, f.y);
+                    const float y = mlp_tile16_step(sm.m, f.x, f.y);
                     wave_lds_sync();
                     if (lane < 16 && e < net_tot) io[e].x = y;
                     wave_lds_sync();
