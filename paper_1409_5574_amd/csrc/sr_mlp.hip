@@ -36,17 +36,57 @@ __device__ __forceinline__ float dsilu(float z) {
     return sg * (1.0f + z * (1.0f - sg));
 }
 
+// The network in LDS, as 16-byte fragments per lane: W2, W3 (outputs along the lanes)
+// and their transposes.  (As rows of 64 the sixteen lanes of a fragment's rows met on
+// two banks.)  What the training reads of a tile's turned-over activations lies in rows
+// of kTbRow values, an odd number of 16-byte units apart, for the same reason.
 struct alignas(16) TrainSmem {
-    MlpSmem m;
-    alignas(16) __bf16 W2T[kH * kH];   // W2T[k][j] = W2[j][k]
-    alignas(16) __bf16 W3T[kH * kH];
+    bf16x8 W2[4][2][64], W3[4][2][64], W2T[4][2][64], W3T[4][2][64];
+    float W1[2 * kH];
+    float b1[kH], b2[kH], b3[kH], W4[kH];
+    float b4;
 };
+constexpr int kTbRow = kH + 8;
+
+// Every load of the block is in flight before the first is used.
+__device__ __forceinline__ void mlp_load_train(TrainSmem &s, const __bf16 *__restrict__ p, int tid,
+                                               int nt) {
+    constexpr int kPer = 4;          // 16-byte pieces a thread
+    bf16x8 v[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * nt, layer = i >> 9, e = i & 511;   // e: row e / 8, columns 8 (e mod 8)
+        v[q] = *(const bf16x8 *)(p + (layer ? kOffW3 : kOffW2) + 8 * e);
+    }
+    for (int i = tid; i < 2 * kH; i += nt) s.W1[i] = (float)p[kOffW1 + i];
+    for (int i = tid; i < kH; i += nt) {
+        s.b1[i] = (float)p[kOffB1 + i];
+        s.b2[i] = (float)p[kOffB2 + i];
+        s.b3[i] = (float)p[kOffB3 + i];
+        s.W4[i] = (float)p[kOffW4 + i];
+    }
+    if (tid == 0) s.b4 = (float)p[kOffB4];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int i = tid + q * nt, layer = i >> 9, e = i & 511;
+        const int row = e >> 3, col = 8 * (e & 7);
+        (layer ? s.W3 : s.W2)[row >> 4][col >> 5][(row & 15) + 16 * ((col >> 3) & 3)] = v[q];
+        __bf16 *t = (__bf16 *)(layer ? s.W3T : s.W2T)[col >> 4][row >> 5] + (row & 7);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) t[8 * ((col & 15) + c + 16 * ((row >> 3) & 3))] = v[q][c];
+    }
+}
 
 // Gradient of L = (1/M) sum w (y - t)^2, w = x / E[x] (the energy weighting of
 // the binned spectrum the network is judged on), for this kernel's tiles; with
 // VJP, the gradient of sum dout * y instead (`target` holds dout, inv_m unused).
 // Each wave accumulates its own gradient and writes it to work[wave_global][...]
 // (summed in a fixed order by grad_reduce).
+//
+// One wave per SIMD (the accumulators and the tile's state are 344 registers), so what
+// a step costs is the latency of a block's start and end and the LDS: 65 536 samples,
+// four tiles a wave, take 32 us; 35.5 us with the weights fetched and turned over
+// value by value and their rows, and the activations' transposes, on two LDS banks.
 template <bool VJP>
 __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restrict__ params,
                                                            const float2 *__restrict__ feats,
@@ -54,13 +94,9 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
                                                            int64_t M, float inv_m,
                                                            float *__restrict__ work) {
     __shared__ TrainSmem s;
-    __shared__ alignas(16) __bf16 tbuf[kWaves][2 * 16 * kH];
-    mlp_load(s.m, params, threadIdx.x, blockDim.x);
-    for (int i = threadIdx.x; i < kH * kH; i += blockDim.x) {
-        const int j = i / kH, k = i % kH;
-        s.W2T[k * kH + j] = params[kOffW2 + i];
-        s.W3T[k * kH + j] = params[kOffW3 + i];
-    }
+    __shared__ alignas(16) __bf16 tbuf[kWaves][2 * 16 * kTbRow];
+    static_assert(kBlock * 4 * 8 == 2 * kH * kH, "four pieces a thread");
+    mlp_load_train(s, params, threadIdx.x, kBlock);
     __syncthreads();
     const int wave = threadIdx.x >> 6, l = threadIdx.x & 63, r = l & 15, g = l >> 4;
     __bf16 *tb = tbuf[wave];
@@ -99,7 +135,7 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
                 const int k = 32 * kb + 8 * g + e;
-                split_set(a[kb], e, silu(fmaf(s.m.W1[2 * k], f.x, fmaf(s.m.W1[2 * k + 1], f.y, s.m.b1[k]))));
+                split_set(a[kb], e, silu(fmaf(s.W1[2 * k], f.x, fmaf(s.W1[2 * k + 1], f.y, s.b1[k]))));
             }
         float z1[4][4];   // z1[n][q]: sample 4g+q, feature 16n+r
 #pragma unroll
@@ -107,7 +143,7 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             const int k = 16 * n + r;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
-                z1[n][q] = fmaf(s.m.W1[2 * k], fq0[q], fmaf(s.m.W1[2 * k + 1], fq1[q], s.m.b1[k]));
+                z1[n][q] = fmaf(s.W1[2 * k], fq0[q], fmaf(s.W1[2 * k + 1], fq1[q], s.b1[k]));
         }
         f32x4 z2[4];
 #pragma unroll
@@ -115,11 +151,11 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             z2[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 b = *(const bf16x8 *)&s.m.W2[(16 * n + r) * kH + 32 * kb + 8 * g];
+                const bf16x8 b = s.W2[n][kb][l];
                 z2[n] = mfma_split(a[kb], b, z2[n]);
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) z2[n][q] += s.m.b2[16 * n + r];
+            for (int q = 0; q < 4; ++q) z2[n][q] += s.b2[16 * n + r];
         }
 #pragma unroll
         for (int n = 0; n < 4; ++n)
@@ -127,14 +163,14 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             for (int q = 0; q < 4; ++q) {
                 const float v = silu(z2[n][q]);
                 const __bf16 h = (__bf16)v;
-                tb[(4 * g + q) * kH + 16 * n + r] = h;
-                tb[16 * kH + (4 * g + q) * kH + 16 * n + r] = (__bf16)(v - (float)h);
+                tb[(4 * g + q) * kTbRow + 16 * n + r] = h;
+                tb[(16 + 4 * g + q) * kTbRow + 16 * n + r] = (__bf16)(v - (float)h);
             }
         wave_lds_sync();
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
-            a[kb].hi = *(const bf16x8 *)&tb[r * kH + 32 * kb + 8 * g];
-            a[kb].lo = *(const bf16x8 *)&tb[16 * kH + r * kH + 32 * kb + 8 * g];
+            a[kb].hi = *(const bf16x8 *)&tb[r * kTbRow + 32 * kb + 8 * g];
+            a[kb].lo = *(const bf16x8 *)&tb[(16 + r) * kTbRow + 32 * kb + 8 * g];
         }
         wave_lds_sync();
         f32x4 z3[4];
@@ -143,17 +179,17 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             z3[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 b = *(const bf16x8 *)&s.m.W3[(16 * n + r) * kH + 32 * kb + 8 * g];
+                const bf16x8 b = s.W3[n][kb][l];
                 z3[n] = mfma_split(a[kb], b, z3[n]);
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) z3[n][q] += s.m.b3[16 * n + r];
+            for (int q = 0; q < 4; ++q) z3[n][q] += s.b3[16 * n + r];
         }
         float sq[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sq[q] = fmaf(s.m.W4[16 * n + r], silu(z3[n][q]), sq[q]);
+            for (int q = 0; q < 4; ++q) sq[q] = fmaf(s.W4[16 * n + r], silu(z3[n][q]), sq[q]);
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
@@ -169,7 +205,7 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             } else {
                 // energy weighting: each sample counts with x / E[x] (E[x] = 8/(15 sqrt3) ...)
                 const float wq = exp2f(tq) * 3.2475953f;
-                dyq[q] = vq ? 2.0f * inv_m * wq * (sq[q] + s.m.b4 - tq) : 0.f;
+                dyq[q] = vq ? 2.0f * inv_m * wq * (sq[q] + s.b4 - tq) : 0.f;
             }
         }
         if (r == 0) gb4 += dyq[0] + dyq[1] + dyq[2] + dyq[3];
@@ -177,7 +213,7 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
         f32x4 dz3[4];
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
-            const float w4 = s.m.W4[16 * n + r];
+            const float w4 = s.W4[16 * n + r];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 gW4[n] = fmaf(dyq[q], silu(z3[n][q]), gW4[n]);
@@ -203,10 +239,10 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
 #pragma unroll
         for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) tb[(4 * g + q) * kH + 16 * n + r] = dz3b[n][q];
+            for (int q = 0; q < 4; ++q) tb[(4 * g + q) * kTbRow + 16 * n + r] = dz3b[n][q];
         wave_lds_sync();
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) a[kb].hi = *(const bf16x8 *)&tb[r * kH + 32 * kb + 8 * g];
+        for (int kb = 0; kb < 2; ++kb) a[kb].hi = *(const bf16x8 *)&tb[r * kTbRow + 32 * kb + 8 * g];
         wave_lds_sync();
         f32x4 dz2[4];
 #pragma unroll
@@ -214,7 +250,7 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             dz2[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 b = *(const bf16x8 *)&s.W3T[(16 * n + r) * kH + 32 * kb + 8 * g];
+                const bf16x8 b = s.W3T[n][kb][l];
                 dz2[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kb].hi, b, dz2[n], 0, 0, 0);
             }
 #pragma unroll
@@ -241,17 +277,17 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
 #pragma unroll
         for (int n = 0; n < 4; ++n)
 #pragma unroll
-            for (int q = 0; q < 4; ++q) tb[(4 * g + q) * kH + 16 * n + r] = dz2b[n][q];
+            for (int q = 0; q < 4; ++q) tb[(4 * g + q) * kTbRow + 16 * n + r] = dz2b[n][q];
         wave_lds_sync();
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb) a[kb].hi = *(const bf16x8 *)&tb[r * kH + 32 * kb + 8 * g];
+        for (int kb = 0; kb < 2; ++kb) a[kb].hi = *(const bf16x8 *)&tb[r * kTbRow + 32 * kb + 8 * g];
         wave_lds_sync();
 #pragma unroll
         for (int n = 0; n < 4; ++n) {
             f32x4 dh1 = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 b = *(const bf16x8 *)&s.W2T[(16 * n + r) * kH + 32 * kb + 8 * g];
+                const bf16x8 b = s.W2T[n][kb][l];
                 dh1 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kb].hi, b, dh1, 0, 0, 0);
             }
 #pragma unroll
@@ -300,18 +336,39 @@ __global__ __launch_bounds__(kBlock) void mlp_train_kernel(const __bf16 *__restr
             }
 }
 
-// grads[p] = sum over waves of work[wave][p] (fixed order).
-// Sum of the per-wave gradient rows, in two fixed-order stages: blockIdx.y
-// sums rows [y * per, (y + 1) * per) into out row y.
-__global__ void grad_reduce_kernel(const float *__restrict__ work, int nrows, int per,
-                                   float *__restrict__ out) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= kNParams) return;
-    const int r0 = blockIdx.y * per, r1 = min(r0 + per, nrows);
-    float sum = 0.f;
-#pragma unroll 8
-    for (int w = r0; w < r1; ++w) sum += work[(int64_t)w * kNParams + p];
-    out[(int64_t)blockIdx.y * kNParams + p] = sum;
+// grads[p] = sum over the waves of work[wave][p], in a fixed order: a thread sums
+// kGradGroup consecutive rows, and one thread a parameter adds those sums.  (The order
+// is part of what a training run gives: thousands of steps amplify a rounding.)  The
+// 35 MB of 1024 rows take 8.7 us in one launch; 12.3 us in a launch for each level,
+// and 12.4 us with 32 parameters a block, whose 128-byte pieces of the odd-length rows
+// lie on two cache lines each.
+constexpr int kGradGroup = 32, kGradGroups = 32;
+constexpr int kGradPer = 64, kGradThreads = 1024, kGradEach = kGradGroups * kGradPer / kGradThreads;
+__global__ __launch_bounds__(kGradThreads) void grad_reduce_kernel(const float *__restrict__ work,
+                                                                   int rows,
+                                                                   float *__restrict__ grads) {
+    __shared__ float part[kGradGroups][kGradPer];
+    const int c = threadIdx.x % kGradPer;
+    const int p = min((int)blockIdx.x * kGradPer + c, kNParams - 1);
+#pragma unroll
+    for (int h = 0; h < kGradEach; ++h) {
+        const int y = threadIdx.x / kGradPer + h * (kGradThreads / kGradPer);
+        const int r0 = y * kGradGroup, r1 = min(r0 + kGradGroup, rows);
+        float sum = 0.f;
+        if (r1 - r0 == kGradGroup) {
+#pragma unroll
+            for (int w = 0; w < kGradGroup; ++w) sum += work[(int64_t)(r0 + w) * kNParams + p];
+        } else {
+            for (int w = r0; w < r1; ++w) sum += work[(int64_t)w * kNParams + p];
+        }
+        part[y][c] = sum;
+    }
+    __syncthreads();
+    if (threadIdx.x < kGradPer && (int)blockIdx.x * kGradPer + c < kNParams) {
+        float sum = 0.f;
+        for (int q = 0; q * kGradGroup < rows; ++q) sum += part[q][c];
+        grads[p] = sum;
+    }
 }
 
 __global__ void adam_kernel(float *__restrict__ master, __bf16 *__restrict__ params,
@@ -366,7 +423,6 @@ __global__ void eval_direct_kernel(TableDev tab, const uint32_t *__restrict__ a,
 }
 
 constexpr int kTrainBlocks = 256;      // one block (four waves, one per SIMD) per CU
-constexpr int kGradGroups = 32;        // first-stage row groups of the gradient sum
 
 // ------------------------------------------------------------------ the judge
 // Sample s of the judge's stratified grid: chi-bin b (of kMlpFallbackBins on
@@ -459,18 +515,18 @@ __global__ void zero_doubles_kernel(double *__restrict__ p, int64_t n) {
 
 int launch_grad(bool vjp, const void *params, const float *feats, const float *target, int64_t M,
                 float *grads, float *work, hipStream_t st) {
+    // no block without a tile: its rows of zeros would be written and read again
+    const int64_t tiles = (M + 15) / 16;
+    const int nb = (int)std::min<int64_t>(kTrainBlocks, (tiles + kWaves - 1) / kWaves);
     if (vjp)
-        mlp_train_kernel<true><<<kTrainBlocks, kBlock, 0, st>>>(
-            (const __bf16 *)params, (const float2 *)feats, target, M, 1.0f / (float)M, work);
+        mlp_train_kernel<true><<<nb, kBlock, 0, st>>>((const __bf16 *)params, (const float2 *)feats,
+                                                      target, M, 1.0f / (float)M, work);
     else
-        mlp_train_kernel<false><<<kTrainBlocks, kBlock, 0, st>>>(
-            (const __bf16 *)params, (const float2 *)feats, target, M, 1.0f / (float)M, work);
-    const int rows = kTrainBlocks * kWaves, per = rows / kGradGroups;
-    float *mid = work + (int64_t)rows * kNParams;
-    grad_reduce_kernel<<<dim3((kNParams + 255) / 256, kGradGroups), 256, 0, st>>>(work, rows, per,
-                                                                                  mid);
-    grad_reduce_kernel<<<dim3((kNParams + 255) / 256, 1), 256, 0, st>>>(mid, kGradGroups,
-                                                                        kGradGroups, grads);
+        mlp_train_kernel<false><<<nb, kBlock, 0, st>>>((const __bf16 *)params, (const float2 *)feats,
+                                                       target, M, 1.0f / (float)M, work);
+    static_assert(kTrainBlocks * kWaves <= kGradGroup * kGradGroups, "rows of the gradient sum");
+    grad_reduce_kernel<<<(kNParams + kGradPer - 1) / kGradPer, kGradThreads, 0, st>>>(
+        work, nb * kWaves, grads);
     SR_HIP_CHECK(hipGetLastError());
     return SR_OK;
 }
@@ -494,7 +550,8 @@ extern "C" int sr_mlp_forward(const void *params, const float *feats, float *out
 }
 
 extern "C" int64_t sr_mlp_grad_work(void) {
-    return ((int64_t)kTrainBlocks * kWaves + kGradGroups) * kNParams;
+    // (32 rows more than in use: callers keep workspaces of this size)
+    return ((int64_t)kTrainBlocks * kWaves + 32) * kNParams;
 }
 
 extern "C" int sr_mlp_mse_grad(const void *params, const float *feats, const float *target,

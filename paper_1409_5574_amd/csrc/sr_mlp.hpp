@@ -26,14 +26,6 @@ constexpr int kMlpFallbackBins = 24;
 constexpr float kMlpChiLo = -4.0f, kMlpChiHi = 2.0f;
 constexpr float kMlpLog2xFloor = -16.609640f;   // training targets clipped at x = 1e-5
 
-struct alignas(16) MlpSmem {
-    alignas(16) __bf16 W2[kH * kH];   // row j holds the weights of output j
-    alignas(16) __bf16 W3[kH * kH];
-    float W1[2 * kH];
-    float b1[kH], b2[kH], b3[kH], W4[kH];
-    float b4;
-};
-
 __device__ __forceinline__ float silu(float z) {
     return z * __builtin_amdgcn_rcpf(1.0f + __expf(-z));
 }
@@ -42,21 +34,6 @@ __device__ __forceinline__ float silu(float z) {
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
     __builtin_amdgcn_wave_barrier();
-}
-
-__device__ __forceinline__ void mlp_load(MlpSmem &s, const __bf16 *__restrict__ p, int tid, int nt) {
-    for (int i = tid; i < kH * kH / 8; i += nt) {
-        ((bf16x8 *)s.W2)[i] = *(const bf16x8 *)(p + kOffW2 + 8 * i);
-        ((bf16x8 *)s.W3)[i] = *(const bf16x8 *)(p + kOffW3 + 8 * i);
-    }
-    for (int i = tid; i < 2 * kH; i += nt) s.W1[i] = (float)p[kOffW1 + i];
-    for (int i = tid; i < kH; i += nt) {
-        s.b1[i] = (float)p[kOffB1 + i];
-        s.b2[i] = (float)p[kOffB2 + i];
-        s.b3[i] = (float)p[kOffB3 + i];
-        s.W4[i] = (float)p[kOffW4 + i];
-    }
-    if (tid == 0) s.b4 = (float)p[kOffB4];
 }
 
 // Activations enter the matrix cores as a pair of bfloat16 values (hi + lo,
