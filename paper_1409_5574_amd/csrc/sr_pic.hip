@@ -12,6 +12,8 @@
 //     B -= (dt/2) curl E;   E += dt (curl B - J);   B -= (dt/2) curl E.
 #include <math.h>
 
+#include <type_traits>
+
 #include "sr_common.hpp"
 
 namespace sr {
@@ -166,56 +168,92 @@ __device__ __forceinline__ float cic_w(float r, int c) {
     return fmaxf(0.0f, 1.0f - fabsf(r - (float)(c - 1)));
 }
 
+// A cell unwrapped across the periodic boundary to the copy nearest the block's first
+// particle's.
+__device__ __forceinline__ int unwrap_cell(int i, int ref, int n) {
+    int d = i - ref;
+    if (2 * d > n) d -= n;
+    else if (2 * d < -n) d += n;
+    return ref + d;
+}
+
 // A deposit block first finds the box of nodes its particles touch, with cells
 // taken relative to the block's first particle across the periodic boundary (a
 // block whose sorted particles run from the end of one tile row into the next
 // keeps a compact box).  A box above `cap` nodes (particles that have drifted
-// far since the last sort) shrinks, widest axis first, to a window of at most
-// `cap` nodes about the block's mean cell; the particles whose nodes leave the
-// window add to the grid directly.
-template <int WAVES>
+// far since the last sort) is taken in up to kDepSlabs slabs along its widest axis,
+// each particle in the slab of its cell, with the LDS of one: that costs the slabs'
+// common nodes twice, where a particle outside the box adds to the grid by itself.
+// A box too large for that (an unsorted ensemble) shrinks, widest axis first, to a
+// window of at most `cap` nodes about the block's mean cell; the particles whose
+// nodes leave the window add to the grid directly.
 struct DepShared {
-    int red[2][3][WAVES];
-    float bmax[WAVES];
-    int ref[3];
-    float msum[3][WAVES];
-    int mcnt[WAVES];
+    int ref[3], lo[3], hi[3];   // first particle's cell; smallest and largest unwrapped cells
+    uint32_t bmax;              // largest bound, as bits (no bound is negative)
+    float sum[3];               // window only: sums of the cells relative to ref
+    int cnt;
 };
 struct DepBox {
     int org[3], ext[3];   // first node (unwrapped) and extent on each axis
     float bnd;            // the block's largest bound (infinite if one is not finite)
+    int slabs, axis, per; // slabs of `per` cells along `axis`
 };
+constexpr int kDepSlabs = 8;
+
+// Slab t of the box (the box itself if there is one): its own box, and whether it is
+// the slab of the cell U.
+template <int DIM>
+__device__ __forceinline__ bool deposit_slab(const DepBox &bx, int t, int below, int above,
+                                             const int U[3], DepBox &w) {
+    w = bx;
+    if (bx.slabs == 1) return true;
+    bool mine = false;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        if (a != bx.axis) continue;
+        const int first = t * bx.per, c = U[a] - (bx.org[a] + below) - first;
+        w.org[a] = bx.org[a] + first;
+        w.ext[a] = min(bx.per, bx.ext[a] - below - above - first) + below + above;
+        mine = c >= 0 && c < bx.per;
+    }
+    return mine;
+}
 
 // The box of the block's live particles: I their cells, `bound` >= 0 a bound on
 // each one's contributions; nodes reach from `below` under the smallest cell to
 // `above` over the largest.  U receives the particle's unwrapped cell.  False
 // when no particle is live.  Call with the whole block (thread 0 active).
-template <int DIM, int WAVES>
-__device__ __forceinline__ bool deposit_box(DepShared<WAVES> &sh, const int I[3], bool live,
-                                            float bound, const PicGrid &G, int below, int above,
-                                            int cap, int U[3], DepBox &bx) {
-    if (threadIdx.x == 0)
-        for (int a = 0; a < 3; ++a) sh.ref[a] = I[a];
+template <int DIM>
+__device__ __forceinline__ bool deposit_box(DepShared &sh, const int I[3], bool live, float bound,
+                                            const PicGrid &G, int below, int above, int cap, int U[3],
+                                            DepBox &bx) {
+    if (threadIdx.x == 0) {
+        for (int a = 0; a < 3; ++a) {
+            sh.ref[a] = I[a];
+            sh.lo[a] = 0x3fffffff;
+            sh.hi[a] = -0x3fffffff;
+            sh.sum[a] = 0.0f;
+        }
+        sh.bmax = 0;
+        sh.cnt = 0;
+    }
     __syncthreads();
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        int d = I[a] - sh.ref[a];
-        if (a < DIM) {
-            if (2 * d > G.n[a]) d -= G.n[a];
-            else if (2 * d < -G.n[a]) d += G.n[a];
-        }
-        U[a] = sh.ref[a] + d;
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int a = 0; a < 3; ++a) U[a] = a < DIM ? unwrap_cell(I[a], sh.ref[a], G.n[a]) : I[a];
+    const int lane = threadIdx.x & 63;
+    // wave reductions, then one LDS atomic a wave: every thread reads one value each
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
         const int lo = wave_min_i(live ? U[a] : 0x3fffffff);
         const int hi = wave_max_i(live ? U[a] : -0x3fffffff);
-        if (lane == 0) { sh.red[0][a][wave] = lo; sh.red[1][a][wave] = hi; }
+        if (lane == 0) {
+            atomicMin(&sh.lo[a], lo);
+            atomicMax(&sh.hi[a], hi);
+        }
     }
     {
         const float b = wave_max(live ? (bound <= 3.0e38f ? bound : __builtin_inff()) : 0.0f);
-        if (lane == 0) sh.bmax[wave] = b;
+        if (lane == 0) atomicMax(&sh.bmax, __float_as_uint(b));
     }
     __syncthreads();
     bool any = true;
@@ -224,28 +262,43 @@ __device__ __forceinline__ bool deposit_box(DepShared<WAVES> &sh, const int I[3]
         bx.org[a] = 0;
         bx.ext[a] = 1;
         if (a >= DIM) continue;
-        int lo = sh.red[0][a][0], hi = sh.red[1][a][0];
-        for (int w = 1; w < WAVES; ++w) { lo = min(lo, sh.red[0][a][w]); hi = max(hi, sh.red[1][a][w]); }
+        const int lo = sh.lo[a], hi = sh.hi[a];
         any = any && hi >= lo;      // no live particle: lo > hi
         bx.org[a] = lo - below;
         bx.ext[a] = hi - lo + below + above + 1;
     }
-    bx.bnd = sh.bmax[0];
-    for (int w = 1; w < WAVES; ++w) bx.bnd = fmaxf(bx.bnd, sh.bmax[w]);
+    bx.bnd = __uint_as_float(sh.bmax);
     if (!any) return false;
+    bx.slabs = 1;
+    bx.axis = 0;
+    bx.per = 0;
     // volumes in 64 bits: extents can be as large as the grid
     int64_t vol = (int64_t)bx.ext[0] * bx.ext[1] * bx.ext[2];
     if (vol <= cap) return true;
+    {
+        int wide = 0, len = bx.ext[0];
+#pragma unroll
+        for (int b = 1; b < DIM; ++b)
+            if (bx.ext[b] > len) { wide = b; len = bx.ext[b]; }
+        const int per = (int)min<int64_t>(cap / (vol / len), 0x3fffffff) - below - above;
+        const int n_cells = len - below - above;
+        if (per >= 1 && n_cells <= kDepSlabs * per) {
+            bx.axis = wide;
+            bx.slabs = (n_cells + per - 1) / per;
+            bx.per = (n_cells + bx.slabs - 1) / bx.slabs;   // even slabs,
+            bx.slabs = (n_cells + bx.per - 1) / bx.per;     // none of them empty
+            return true;
+        }
+    }
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
         const float v = wave_sum_f(live ? (float)(U[a] - sh.ref[a]) : 0.0f);
-        if (lane == 0) sh.msum[a][wave] = v;
+        if (lane == 0) atomicAdd(&sh.sum[a], v);
     }
     const int n_live = (int)__popcll(__ballot(live));
-    if (lane == 0) sh.mcnt[wave] = n_live;
+    if (lane == 0) atomicAdd(&sh.cnt, n_live);
     __syncthreads();
-    int cnt = 0;
-    for (int w = 0; w < WAVES; ++w) cnt += sh.mcnt[w];
+    const int cnt = sh.cnt;
     for (int it = 0; it < DIM && vol > cap; ++it) {
         int wide = 0;
 #pragma unroll
@@ -256,9 +309,7 @@ __device__ __forceinline__ bool deposit_box(DepShared<WAVES> &sh, const int I[3]
             if (a != wide) continue;
             const int64_t other = vol / bx.ext[a];
             const int wdt = (int)min<int64_t>(bx.ext[a], max<int64_t>(4, cap / other));
-            float sum = 0.0f;
-            for (int w = 0; w < WAVES; ++w) sum += sh.msum[a][w];
-            const int c = sh.ref[a] + (int)floorf(sum / (float)max(cnt, 1) + 0.5f);
+            const int c = sh.ref[a] + (int)floorf(sh.sum[a] / (float)max(cnt, 1) + 0.5f);
             bx.org[a] = min(max(c - wdt / 2, bx.org[a]), bx.org[a] + bx.ext[a] - wdt);
             bx.ext[a] = wdt;
             vol = other * wdt;
@@ -267,20 +318,26 @@ __device__ __forceinline__ bool deposit_box(DepShared<WAVES> &sh, const int I[3]
     return true;
 }
 
-// Grid index of box node l (x fastest), wrapped onto the periodic grid: the
-// nodes lie in [-n/2 - 1, 3n/2 + 1], so two wraps each way reach [0, n) for
-// any n.
+// The grid index of the first node of each row (y, z) of the box, wrapped onto the
+// periodic grid: the nodes lie in [-n/2 - 1, 3n/2 + 1], so two wraps each way reach
+// [0, n) for any n.  Call with the whole block, and synchronise after it.
 template <int DIM>
-__device__ __forceinline__ uint32_t box_node(int l, const DepBox &bx, float inv_e0, float inv_e1,
+__device__ __forceinline__ void box_rows(uint32_t *row, const DepBox &bx, const PicGrid &G) {
+    const float inv_e1 = 1.0f / (float)bx.ext[1];
+    for (int r = threadIdx.x; r < bx.ext[1] * bx.ext[2]; r += blockDim.x) {
+        const int lk = div_small(r, bx.ext[1], inv_e1), lj = r - lk * bx.ext[1];
+        int j = wrap2(bx.org[1] + lj, G.n[1]), k = DIM == 3 ? wrap2(bx.org[2] + lk, G.n[2]) : 0;
+        j = min(max(j, 0), G.n[1] - 1);
+        k = min(max(k, 0), G.n[2] - 1);
+        row[r] = cell(0, j, k, G);
+    }
+}
+// Grid index of box node l (x fastest).
+__device__ __forceinline__ uint32_t box_node(int l, const uint32_t *row, const DepBox &bx, float inv_e0,
                                              const PicGrid &G) {
-    const int r = div_small(l, bx.ext[0], inv_e0), li = l - r * bx.ext[0];
-    const int lk = div_small(r, bx.ext[1], inv_e1), lj = r - lk * bx.ext[1];
-    int i = wrap2(bx.org[0] + li, G.n[0]), j = wrap2(bx.org[1] + lj, G.n[1]);
-    int k = DIM == 3 ? wrap2(bx.org[2] + lk, G.n[2]) : 0;
-    i = min(max(i, 0), G.n[0] - 1);
-    j = min(max(j, 0), G.n[1] - 1);
-    k = min(max(k, 0), G.n[2] - 1);
-    return cell(i, j, k, G);
+    const int r = div_small(l, bx.ext[0], inv_e0);
+    const int i = wrap2(bx.org[0] + l - r * bx.ext[0], G.n[0]);
+    return row[r] + (uint32_t)min(max(i, 0), G.n[0] - 1);
 }
 
 // Charge: rho += q w S / dV on the 4 (2D) or 8 (3D) nodes of each particle.
@@ -298,15 +355,15 @@ __device__ __forceinline__ uint32_t box_node(int l, const DepBox &bx, float inv_
 // is exact too: a node's block sum is rounded once.  A block most of whose
 // particles lie outside the window (an unsorted ensemble) goes direct.
 //
-// The 4.0 M sorted electrons at 1/4 per cell on 256^3 take 145 us where the direct
-// adds took 763 us.  At that density a block's box is 6 nodes a particle whatever
-// its size, so small blocks win as long as a block that straddles two tile rows
-// keeps most of its particles in the window: the sort and the deposit took 279 us
-// with 256 particles and 4096 nodes; 284, 300 us with 3072, 5120 nodes; 292 us with
-// 128 and 2048; 333 us with 512 and 6144; 497 us with 1024 and 7936.
+// The sort and the deposit of 4.0 M electrons at 1/4 per cell on 256^3 take 263 us
+// where the direct adds took 896.  At that density a block's box is 6 nodes a particle
+// whatever its size, so small blocks win as long as a block that straddles two tile
+// rows keeps to one or two slabs: 292 us with 128 particles and 2048 nodes, 333 with 512
+// and 6144, 497 with 1024 and 7936.  With 256 the blocks in flight decide: five a
+// compute unit with 3072 nodes; 266 and 268 us with four and 3840 or 3584, 285 with
+// 4096 nodes and the 88 registers the compiler takes by itself.
 constexpr int kRhoThreads = 256;   // particles per block
-constexpr int kRhoWaves = kRhoThreads / 64;
-constexpr int kRhoCells = 4096;    // 32 KB: four blocks per compute unit
+constexpr int kRhoCells = 3072;    // 24 KB and 6 KB of rows: five blocks per compute unit
 constexpr int kRhoBits = 44;
 
 // v 2^s as a 64-bit integer, for |v 2^s| < 2^51: the sum with 1.5 2^52 leaves
@@ -317,10 +374,11 @@ __device__ __forceinline__ unsigned long long fixed64(float v, double scale) {
 }
 
 template <int DIM>
-__global__ __launch_bounds__(kRhoThreads) void rho_kernel(sr_particles_f32 P, PicGrid G, float qv,
+__global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))) void rho_kernel(sr_particles_f32 P, PicGrid G, float qv,
                                                           float *__restrict__ rho) {
     __shared__ unsigned long long box[kRhoCells];
-    __shared__ DepShared<kRhoWaves> sh;
+    __shared__ uint32_t row[kRhoCells / 2];      // a box is at least 2 nodes wide
+    __shared__ DepShared sh;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = p < P.n;
     const uint32_t u = active ? (uint32_t)p : 0u;
@@ -364,39 +422,52 @@ __global__ __launch_bounds__(kRhoThreads) void rho_kernel(sr_particles_f32 P, Pi
     int e = 0;
     (void)frexpf(bx.bnd, &e);      // bnd < 2^e
     const double to_fix = ldexp(1.0, kRhoBits - e), from_fix = ldexp(1.0, e - kRhoBits);
-    const int cells = bx.ext[0] * bx.ext[1] * bx.ext[2];
-    for (int q = threadIdx.x; q < cells; q += kRhoThreads) box[q] = 0;
-    __syncthreads();
-    if (in_win) {
-        const int l0 = (U[0] - bx.org[0]) +
-                       bx.ext[0] * ((U[1] - bx.org[1]) + bx.ext[1] * (DIM == 3 ? U[2] - bx.org[2] : 0));
-        each([&](int a, int b, int c, float v) {
-            atomicAdd(&box[l0 + a + bx.ext[0] * (b + bx.ext[1] * c)], fixed64(v, to_fix));
-        });
-    }
-    __syncthreads();
-    const float inv_e0 = 1.0f / (float)bx.ext[0], inv_e1 = 1.0f / (float)bx.ext[1];
-    for (int q = threadIdx.x; q < cells; q += kRhoThreads) {
-        const long long sum = (long long)box[q];
-        if (sum != 0)
-            unsafeAtomicAdd(&rho[box_node<DIM>(q, bx, inv_e0, inv_e1, G)], (float)((double)sum * from_fix));
+    for (int t = 0; t < bx.slabs; ++t) {
+        DepBox w;
+        const bool mine = deposit_slab<DIM>(bx, t, 0, 1, U, w) && in_win;
+        const int cells = w.ext[0] * w.ext[1] * w.ext[2];
+        if (t) __syncthreads();        // the box is flushed
+        for (int q = threadIdx.x; q < cells; q += kRhoThreads) box[q] = 0;
+        box_rows<DIM>(row, w, G);
+        __syncthreads();
+        if (mine) {
+            const int l0 = (U[0] - w.org[0]) +
+                           w.ext[0] * ((U[1] - w.org[1]) + w.ext[1] * (DIM == 3 ? U[2] - w.org[2] : 0));
+            each([&](int a, int b, int c, float v) {
+                atomicAdd(&box[l0 + a + w.ext[0] * (b + w.ext[1] * c)], fixed64(v, to_fix));
+            });
+        }
+        __syncthreads();
+        const float inv_e0 = 1.0f / (float)w.ext[0];
+        for (int q = threadIdx.x; q < cells; q += kRhoThreads) {
+            const long long sum = (long long)box[q];
+            if (sum != 0)
+                unsafeAtomicAdd(&rho[box_node(q, row, w, inv_e0, G)], (float)((double)sum * from_fix));
+        }
     }
 }
 
 // Esirkepov's current of the move x_old -> x (one lane per particle).  On each
 // axis the old shape S0 and the new shape S1 of a move below one cell lie on
-// three consecutive nodes among i-1 .. i+2 of the old cell i, and the loops
-// run over those three; D = S1 - S0.  Per node of the stencil
+// three consecutive nodes among i-1 .. i+2 of the old cell i; D = S1 - S0.  Per node
+// of the stencil
 //   3D  W_x = Dx (S0y S0z + Dy S0z/2 + S0y Dz/2 + Dy Dz/3)  (and cyclically),
 //   Jx(i+1/2) = Jx(i-1/2) - q w (dx/dt) W_x / dV, summed along x;
 //   2D  W_x = Dx (S0y + Dy/2),  W_y = Dy (S0x + Dx/2),
 //       Jz = q w v_z (S0x S0y + Dx S0y/2 + S0x Dy/2 + Dx Dy/3) / dV on the nodes.
-// Zero contributions are skipped.  A move of a cell or more sets *status.
+// A move of a cell or more sets *status.
+//
+// Most moves stay in their cell.  Then S0 and S1 share two nodes, D = (-du, du) with
+// du the move in cells, and only the first partial sum along an axis is not zero: 12
+// contributions a particle in 3D, 8 in 2D, where the general stencil has 54 (3D) and,
+// with some lane of nearly every wave crossing a cell face, every wave paid for them
+// all.  Each block adds the moves that stay at once and lists the others, which it then
+// takes densely, 64 to a wave.
 //
 // Sorted particles put the lanes of a block on the same few cells, where
 // global float atomics serialise: the block accumulates in its LDS box
 // (deposit_box, kDepCells cells, three components) and adds the box's non-zero
-// entries to the grid at the end.
+// entries to the grid at the end, the three components of a node together.
 //
 // The box holds fixed-point integers, not floats: on gfx950 an LDS float
 // atomic add takes about 40 times as long as an integer one, and it was the
@@ -412,62 +483,57 @@ __global__ __launch_bounds__(kRhoThreads) void rho_kernel(sr_particles_f32 P, Pi
 // exact sum of its n <= 512 contributions.  That bound is absolute: a node
 // whose current is far below B in a block that also holds a much heavier or
 // faster particle keeps only that absolute accuracy.
+//
+// 2^23 electrons, two a cell, in 4x4x4 tiles take 310 us right after the sort, where
+// the general stencil for all of them took 437; 380 us after 407 steps of a wake, 686
+// before, when a drifted block's particles beyond the window went to the grid one by
+// one.  Of these the blocks' set-up and loads are some 128 us and the entries' atomics
+// some 50.  Bound by latency at that: six waves per SIMD (80 registers; with the 88 that
+// the compiler takes by itself there are only five, and a third block does not fit).
 constexpr int kDepThreads = 512;   // particles per block
-constexpr int kDepWaves = kDepThreads / 64;
 constexpr int kDepCells = 3072;
+constexpr int kDepRows = kDepCells / 4;   // a box is at least 4 nodes wide
 // 2^kDepFracBits units per bound and at most kDepThreads contributions per
 // node: sums stay below 2^30
 constexpr int kDepFracBits = 30 - 9;
 static_assert(kDepThreads == 512, "kDepFracBits assumes 2^9 particles per block");
 
-struct Stencil {
+struct Move {
     int I[3];              // old cell of the particle on each axis
-    int o[3];              // the move's three nodes on each axis: I - 1 + o .. I + 1 + o
-    float S0[3][3], D[3][3];   // old shape and its change on those nodes
+    float f0[3], du[3];    // old fraction in it, move in cells
     float cx, cy, cz;      // -q w (dx_a/dt)/dV (3D), and q w v_z / dV for 2D Jz in cz
     float bound;           // bound on |contribution| (with a margin for rounding)
     bool live;             // active, finite move below one cell
 };
 
+struct Stencil {
+    int o[3];              // the move's three nodes on each axis: I - 1 + o .. I + 1 + o
+    float S0[3][3], D[3][3];   // old shape and its change on those nodes
+    float cx, cy, cz;
+};
+
 template <int DIM>
-__device__ __forceinline__ Stencil make_stencil(const sr_particles_f32 &P, const float *const xo[3],
-                                                const PicGrid &G, float qv, float inv_dt,
-                                                uint32_t u, bool active, bool &bad) {
-    Stencil s;
+__device__ __forceinline__ Move make_move(const sr_particles_f32 &P, const float *const xo[3],
+                                          const PicGrid &G, float qv, float inv_dt, uint32_t u,
+                                          bool active, bool &bad) {
+    Move s;
     s.live = active;
     bad = false;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        s.I[a] = 0;
-        s.o[a] = 1;
-        for (int c = 0; c < 3; ++c) { s.S0[a][c] = (a >= DIM && c == 0) ? 1.0f : 0.0f; s.D[a][c] = 0.0f; }
-    }
+    for (int a = 0; a < 3; ++a) { s.I[a] = 0; s.f0[a] = 0.0f; s.du[a] = 0.0f; }
     s.cx = s.cy = s.cz = 0.0f;
     s.bound = 0.0f;
     if (!active) return s;
     bool ok = true;
-    float du_abs[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
         const float x0 = ld(xo[a], u), x1 = ld(P.x[a], u);
         float d = x1 - x0;                       // the shorter way round the box
         if (d > 0.5f * G.L[a]) d -= G.L[a];
         else if (d < -0.5f * G.L[a]) d += G.L[a];
-        float f0;
-        locate(x0, G.inv_hi[a], G.inv_lo[a], G.n[a], s.I[a], f0);
-        const float du = d * G.inv_hi[a];
-        ok = ok && fabsf(du) < 1.0f;
-        du_abs[a] = fabsf(du);
-        const float r1 = f0 + du;
-        // old shape on nodes i, i+1; new shape on i-1, i (r1 < 0) or on
-        // i, i+1 or i+1, i+2: three nodes from i - 1 + o
-        const int o = r1 < 0.0f ? 0 : 1;
-        s.o[a] = o;
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            s.S0[a][c] = cic_w(f0, c + o);
-            s.D[a][c] = cic_w(r1, c + o) - s.S0[a][c];
-        }
+        locate(x0, G.inv_hi[a], G.inv_lo[a], G.n[a], s.I[a], s.f0[a]);
+        s.du[a] = d * G.inv_hi[a];
+        ok = ok && fabsf(s.du[a]) < 1.0f;
     }
     if (!ok) {
         bad = true;
@@ -488,96 +554,152 @@ __device__ __forceinline__ Stencil make_stencil(const sr_particles_f32 &P, const
     // |v| <= |c_a| |du_a| per axis (2D Jz: |c_z|); the margin covers the
     // rounding of the weights and of their partial sums
     constexpr float kPad = 1.0f / (1 << 20);
-    float b = fmaxf(fabsf(s.cx) * (du_abs[0] + kPad), fabsf(s.cy) * (du_abs[1] + kPad));
-    b = fmaxf(b, DIM == 3 ? fabsf(s.cz) * (du_abs[2] + kPad) : fabsf(s.cz));
+    float b = fmaxf(fabsf(s.cx) * (fabsf(s.du[0]) + kPad), fabsf(s.cy) * (fabsf(s.du[1]) + kPad));
+    b = fmaxf(b, DIM == 3 ? fabsf(s.cz) * (fabsf(s.du[2]) + kPad) : fabsf(s.cz));
     s.bound = b * 1.001f;
     return s;
 }
 
-// Every non-zero contribution of one particle, as add(component, node offsets
-// ci, cj, ck in 0..2 relative to I - 1 + o, value).  Along the component's own
+// The move stays in its cell on every axis.
+template <int DIM>
+__device__ __forceinline__ bool stays(const Move &m) {
+    bool in = true;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const float r1 = m.f0[a] + m.du[a];
+        in = in && r1 >= 0.0f && r1 < 1.0f;
+    }
+    return in;
+}
+
+template <int DIM>
+__device__ __forceinline__ Stencil make_stencil(const Move &m) {
+    Stencil s;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        s.o[a] = 1;
+        for (int c = 0; c < 3; ++c) { s.S0[a][c] = (a >= DIM && c == 0) ? 1.0f : 0.0f; s.D[a][c] = 0.0f; }
+    }
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const float r1 = m.f0[a] + m.du[a];
+        // old shape on nodes i, i+1; new shape on i-1, i (r1 < 0) or on
+        // i, i+1 or i+1, i+2: three nodes from i - 1 + o
+        const int o = r1 < 0.0f ? 0 : 1;
+        s.o[a] = o;
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            s.S0[a][c] = cic_w(m.f0[a], c + o);
+            s.D[a][c] = cic_w(r1, c + o) - s.S0[a][c];
+        }
+    }
+    s.cx = m.cx;
+    s.cy = m.cy;
+    s.cz = m.cz;
+    return s;
+}
+
+// S0 S0' + D S0'/2 + S0 D'/2 + D D'/3, its roundings fixed (both stencils below are one
+// arithmetic).
+__device__ __forceinline__ float cross_factor(float S0, float D, float T0, float E) {
+    return fmaf(D * E, 1.0f / 3.0f, fmaf(E, 0.5f * S0, fmaf(0.5f * D, T0, S0 * T0)));
+}
+
+// The contributions of a move that stays in its cell, as add(component, node offsets
+// ci, cj, ck in 0..1 from cell I, value): those of the general stencil below that can be
+// other than zero (but for the rounding of D), in the same arithmetic.
+template <int DIM, typename ADD>
+__device__ __forceinline__ void esirkepov_stay(const Move &m, ADD &&add) {
+    float S0[3][2], D[3][2];
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        const float r1 = m.f0[a] + m.du[a];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            S0[a][c] = cic_w(m.f0[a], c + 1);
+            D[a][c] = cic_w(r1, c + 1) - S0[a][c];
+        }
+    }
+    const auto cross = [&](int a, int b, int i, int j) {
+        return cross_factor(S0[a][i], D[a][i], S0[b][j], D[b][j]);
+    };
+#pragma unroll
+    for (int k = 0; k < (DIM == 3 ? 2 : 1); ++k)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            if (DIM == 3) {
+                add(0, 0, j, k, m.cx * D[0][0] * cross(1, 2, j, k));
+                add(1, j, 0, k, m.cy * D[1][0] * cross(0, 2, j, k));
+                add(2, j, k, 0, m.cz * D[2][0] * cross(0, 1, j, k));
+            } else {
+                add(0, 0, j, 0, m.cx * D[0][0] * fmaf(0.5f, D[1][j], S0[1][j]));
+                add(1, j, 0, 0, m.cy * D[1][0] * fmaf(0.5f, D[0][j], S0[0][j]));
+                add(2, 0, j, 0, m.cz * cross(0, 1, 0, j));
+                add(2, 1, j, 0, m.cz * cross(0, 1, 1, j));
+            }
+        }
+}
+
+// The contributions of one particle, as add(component, node offsets ci, cj, ck in 0..2
+// relative to I - 1 + o, value); with ALL those that are zero too (an add to LDS costs
+// less than the test).  Along the component's own
 // axis only the first two partial sums are stored: the third is the sum of D,
 // which is zero.
-template <int DIM, typename ADD>
+template <int DIM, bool ALL, typename ADD>
 __device__ __forceinline__ void esirkepov(const Stencil &s, ADD &&add) {
-    if (DIM == 3) {
-        for (int k = 0; k < 3; ++k)
-            for (int j = 0; j < 3; ++j) {
-                const float f = s.S0[1][j] * s.S0[2][k] + 0.5f * s.D[1][j] * s.S0[2][k] +
-                                0.5f * s.S0[1][j] * s.D[2][k] + s.D[1][j] * s.D[2][k] * (1.0f / 3.0f);
-                if (f == 0.0f) continue;
+    // axis A's component on the other axes' nodes (p on axis P, q on axis Q)
+    const auto along = [&](auto A, auto P, auto Q, float c) {
+        constexpr int a = decltype(A)::value, pa = decltype(P)::value, qa = decltype(Q)::value;
+        for (int q = 0; q < (DIM == 3 ? 3 : 1); ++q)
+            for (int p = 0; p < 3; ++p) {
+                const float f = DIM == 3 ? cross_factor(s.S0[pa][p], s.D[pa][p], s.S0[qa][q], s.D[qa][q])
+                                         : fmaf(0.5f, s.D[pa][p], s.S0[pa][p]);
+                if (!ALL && f == 0.0f) continue;
                 float acc = 0.0f;
                 for (int i = 0; i < 2; ++i) {
-                    acc += s.cx * s.D[0][i] * f;
-                    if (acc != 0.0f) add(0, i, j, k, acc);
+                    acc += c * s.D[a][i] * f;
+                    int at[3] = {0, 0, 0};
+                    at[a] = i;
+                    at[pa] = p;
+                    if (DIM == 3) at[qa] = q;
+                    if (ALL || acc != 0.0f) add(a, at[0], at[1], at[2], acc);
                 }
             }
-        for (int k = 0; k < 3; ++k)
-            for (int i = 0; i < 3; ++i) {
-                const float f = s.S0[0][i] * s.S0[2][k] + 0.5f * s.D[0][i] * s.S0[2][k] +
-                                0.5f * s.S0[0][i] * s.D[2][k] + s.D[0][i] * s.D[2][k] * (1.0f / 3.0f);
-                if (f == 0.0f) continue;
-                float acc = 0.0f;
-                for (int j = 0; j < 2; ++j) {
-                    acc += s.cy * s.D[1][j] * f;
-                    if (acc != 0.0f) add(1, i, j, k, acc);
-                }
-            }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    along(I0{}, I1{}, I2{}, s.cx);
+    along(I1{}, I0{}, I2{}, s.cy);
+    if (DIM == 3) {
+        along(I2{}, I0{}, I1{}, s.cz);
+    } else if (s.cz != 0.0f) {
         for (int j = 0; j < 3; ++j)
             for (int i = 0; i < 3; ++i) {
-                const float f = s.S0[0][i] * s.S0[1][j] + 0.5f * s.D[0][i] * s.S0[1][j] +
-                                0.5f * s.S0[0][i] * s.D[1][j] + s.D[0][i] * s.D[1][j] * (1.0f / 3.0f);
-                if (f == 0.0f) continue;
-                float acc = 0.0f;
-                for (int k = 0; k < 2; ++k) {
-                    acc += s.cz * s.D[2][k] * f;
-                    if (acc != 0.0f) add(2, i, j, k, acc);
-                }
+                const float wt = cross_factor(s.S0[0][i], s.D[0][i], s.S0[1][j], s.D[1][j]);
+                if (ALL || wt != 0.0f) add(2, i, j, 0, s.cz * wt);
             }
-    } else {
-        for (int j = 0; j < 3; ++j) {
-            const float f = s.S0[1][j] + 0.5f * s.D[1][j];
-            if (f == 0.0f) continue;
-            float acc = 0.0f;
-            for (int i = 0; i < 2; ++i) {
-                acc += s.cx * s.D[0][i] * f;
-                if (acc != 0.0f) add(0, i, j, 0, acc);
-            }
-        }
-        for (int i = 0; i < 3; ++i) {
-            const float f = s.S0[0][i] + 0.5f * s.D[0][i];
-            if (f == 0.0f) continue;
-            float acc = 0.0f;
-            for (int j = 0; j < 2; ++j) {
-                acc += s.cy * s.D[1][j] * f;
-                if (acc != 0.0f) add(1, i, j, 0, acc);
-            }
-        }
-        if (s.cz != 0.0f)
-            for (int j = 0; j < 3; ++j)
-                for (int i = 0; i < 3; ++i) {
-                    const float wt = s.S0[0][i] * s.S0[1][j] + 0.5f * s.D[0][i] * s.S0[1][j] +
-                                     0.5f * s.S0[0][i] * s.D[1][j] + s.D[0][i] * s.D[1][j] * (1.0f / 3.0f);
-                    if (wt != 0.0f) add(2, i, j, 0, s.cz * wt);
-                }
     }
 }
 
 template <int DIM>
-__global__ __launch_bounds__(kDepThreads) void current_kernel(sr_particles_f32 P, const float *xo0,
+__global__ __launch_bounds__(kDepThreads) __attribute__((amdgpu_waves_per_eu(6))) void current_kernel(sr_particles_f32 P, const float *xo0,
                                                       const float *xo1, const float *xo2,
                                                       PicGrid G, float qv, float inv_dt,
                                                       float *__restrict__ jx, float *__restrict__ jy,
                                                       float *__restrict__ jz,
                                                       uint32_t *__restrict__ status) {
     __shared__ int box[3 * kDepCells];
-    __shared__ DepShared<kDepWaves> sh;
+    __shared__ uint32_t row[kDepRows];
+    __shared__ uint16_t list[kDepThreads];
+    __shared__ int listed;
+    __shared__ DepShared sh;
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = p < P.n;
     const uint32_t u = active ? (uint32_t)p : 0u;
     const float *const xo[3] = {xo0, xo1, xo2};
     bool bad;
-    const Stencil s = make_stencil<DIM>(P, xo, G, qv, inv_dt, u, active, bad);
+    const Move m = make_move<DIM>(P, xo, G, qv, inv_dt, u, active, bad);
     if (bad) atomicOr(status, SR_W_CFL);
     float *const J[3] = {jx, jy, jz};
 
@@ -585,49 +707,95 @@ __global__ __launch_bounds__(kDepThreads) void current_kernel(sr_particles_f32 P
     // ceil(n / kDepThreads) blocks
     int U[3];
     DepBox bx;
-    if (!deposit_box<DIM>(sh, s.I, s.live, s.bound, G, 1, 2, kDepCells, U, bx))
+    if (!deposit_box<DIM>(sh, m.I, m.live, m.bound, G, 1, 2, kDepCells, U, bx))
         return;                     // no live particle (the condition is block-wide)
     const float bnd = bx.bnd;
+    if (!(bnd > 0.0f)) return;      // block-wide: every contribution is zero
     // bnd < 2^e: contributions in units of 2^(e - kDepFracBits).  A
     // non-finite bound, or one so small that 2^(kDepFracBits - e) would not
     // be a finite float, sends the whole block to the float path.
     int e = 0;
-    if (bnd > 0.0f) (void)frexpf(bnd, &e);
+    (void)frexpf(bnd, &e);
     const bool fixed = bnd <= 3.0e38f && e >= -100;
-    bool in_win = s.live && fixed;
+    if (!fixed) bx.slabs = 1;
+    const float to_fix = fixed ? ldexpf(1.0f, kDepFracBits - e) : 0.0f;
+    const float from_fix = fixed ? ldexpf(1.0f, e - kDepFracBits) : 0.0f;
+    const bool in_cell = m.live && fixed && stays<DIM>(m);
+    for (int t = 0; t < bx.slabs; ++t) {
+        DepBox w;
+        const bool mine = deposit_slab<DIM>(bx, t, 1, 2, U, w);
+        const int cells = w.ext[0] * w.ext[1] * w.ext[2];
+        const int e0 = w.ext[0], e01 = w.ext[0] * w.ext[1];
+        if (t) __syncthreads();        // the box is flushed, the list is read
+        if (threadIdx.x == 0) listed = 0;
+        if (fixed) {
+            for (int q = threadIdx.x; q < 3 * cells; q += kDepThreads) box[q] = 0;
+            box_rows<DIM>(row, w, G);
+        }
+        __syncthreads();
+        bool now = in_cell && mine;
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        const int b = U[a] - 1 + s.o[a] - bx.org[a];
-        in_win = in_win && b >= 0 && b + 2 <= bx.ext[a] - 1;
-    }
-    if (s.live && !in_win)
-        esirkepov<DIM>(s, [&](int comp, int ci, int cj, int ck, float v) {
-            const int i = node(s.I[0], s.o[0] + ci, G.n[0]), j = node(s.I[1], s.o[1] + cj, G.n[1]);
-            const int k = DIM == 3 ? node(s.I[2], s.o[2] + ck, G.n[2]) : 0;
-            unsafeAtomicAdd(&J[comp][cell(i, j, k, G)], v);
-        });
-    if (!fixed || !(bnd > 0.0f)) return;      // block-wide; bnd = 0: every contribution is zero
-    const float to_fix = ldexpf(1.0f, kDepFracBits - e), from_fix = ldexpf(1.0f, e - kDepFracBits);
-    const int cells = bx.ext[0] * bx.ext[1] * bx.ext[2];
-    for (int q = threadIdx.x; q < 3 * cells; q += blockDim.x) box[q] = 0;
-    __syncthreads();
-    if (in_win) {
-        const int b0 = U[0] - 1 + s.o[0] - bx.org[0], b1 = U[1] - 1 + s.o[1] - bx.org[1];
-        const int b2 = DIM == 3 ? U[2] - 1 + s.o[2] - bx.org[2] : 0;
-        esirkepov<DIM>(s, [&](int comp, int ci, int cj, int ck, float v) {
-            const int l = (b0 + ci) + bx.ext[0] * ((b1 + cj) + bx.ext[1] * (b2 + ck));
-            atomicAdd(&box[comp * cells + l], __float2int_rn(v * to_fix));
-        });
-    }
-    __syncthreads();
-    const float inv_cells = 1.0f / (float)cells, inv_e0 = 1.0f / (float)bx.ext[0];
-    const float inv_e1 = 1.0f / (float)bx.ext[1];
-    for (int q = threadIdx.x; q < 3 * cells; q += blockDim.x) {
-        const int sum = box[q];
-        if (sum == 0) continue;
-        const int comp = div_small(q, cells, inv_cells);
-        const uint32_t at = box_node<DIM>(q - comp * cells, bx, inv_e0, inv_e1, G);
-        unsafeAtomicAdd(&J[comp][at], (float)sum * from_fix);
+        for (int a = 0; a < DIM; ++a) {
+            const int b = U[a] - w.org[a];
+            now = now && b >= 0 && b + 1 <= w.ext[a] - 1;
+        }
+        if (now) {
+            const int l0 = (U[0] - w.org[0]) + e0 * (U[1] - w.org[1]) +
+                           (DIM == 3 ? e01 * (U[2] - w.org[2]) : 0);
+            esirkepov_stay<DIM>(m, [&](int comp, int ci, int cj, int ck, float v) {
+                atomicAdd(&box[comp * cells + l0 + ci + (cj ? e0 : 0) + (ck ? e01 : 0)],
+                          __float2int_rn(v * to_fix));
+            });
+        }
+        // the slab's others, listed
+        {
+            const bool later = m.live && mine && !now;
+            const uint64_t mask = __ballot(later);
+            int base = 0;
+            if (mask && (threadIdx.x & 63) == 0) base = atomicAdd(&listed, (int)__popcll(mask));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (later) list[base + lane_prefix(mask)] = (uint16_t)threadIdx.x;
+        }
+        __syncthreads();
+        const int n_list = listed;
+        for (int q = threadIdx.x; q < n_list; q += kDepThreads) {
+            bool unused;
+            const uint32_t v = (uint32_t)((int64_t)blockIdx.x * kDepThreads + list[q]);
+            const Move y = make_move<DIM>(P, xo, G, qv, inv_dt, v, true, unused);
+            const Stencil s = make_stencil<DIM>(y);
+            bool in_win = fixed;
+            int B[3] = {0, 0, 0};
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                B[a] = unwrap_cell(y.I[a], sh.ref[a], G.n[a]) - 1 + s.o[a] - w.org[a];
+                in_win = in_win && B[a] >= 0 && B[a] + 2 <= w.ext[a] - 1;
+            }
+            if (in_win)
+                esirkepov<DIM, true>(s, [&](int c, int ci, int cj, int ck, float x) {
+                    const int l = (B[0] + ci) + e0 * (B[1] + cj) + e01 * (B[2] + ck);
+                    atomicAdd(&box[c * cells + l], __float2int_rn(x * to_fix));
+                });
+            else
+                esirkepov<DIM, false>(s, [&](int c, int ci, int cj, int ck, float x) {
+                    const int i = node(y.I[0], s.o[0] + ci, G.n[0]);
+                    const int j = node(y.I[1], s.o[1] + cj, G.n[1]);
+                    const int k = DIM == 3 ? node(y.I[2], s.o[2] + ck, G.n[2]) : 0;
+                    unsafeAtomicAdd(&J[c][cell(i, j, k, G)], x);
+                });
+        }
+        __syncthreads();
+        if (!fixed) return;             // block-wide (one slab: its list held every particle)
+        const float inv_e0 = 1.0f / (float)e0;
+        for (int q = threadIdx.x; q < cells; q += kDepThreads) {
+            int sum[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) sum[c] = box[c * cells + q];
+            if ((sum[0] | sum[1] | sum[2]) == 0) continue;
+            const uint32_t at = box_node(q, row, w, inv_e0, G);
+#pragma unroll
+            for (int c = 0; c < 3; ++c)
+                if (sum[c] != 0) unsafeAtomicAdd(&J[c][at], (float)sum[c] * from_fix);
+        }
     }
 }
 
