@@ -279,10 +279,35 @@ struct LedgerSmem {
 constexpr int kPartCols = SR_LEDGER_COLS + 2;
 constexpr int kPartFlags = SR_LEDGER_COLS;
 
+// How a block takes its particles:
+//   kUniform  one round of 64 for each of its four uniform chunks;
+//   kBox      the same with the LDS field box;
+//   kLoop     explicit chunks, one wave each, as many rounds as its chunk has;
+//   kRagged   explicit chunks, their rounds dealt to the block's waves.
+enum StepMode { kUniform = 0, kBox = 1, kRagged = 2, kLoop = 3 };
+
+// Most explicit chunks for which their rounds are dealt.  That shortens the longest
+// chunks' chains, which is what a launch takes that the chip holds at once; it costs waves
+// in flight (111 registers and up, a list entry a trial), which is what a larger one needs.
+// Random cuts, 60 particles a chunk on average, quantum sampler, one wave a chunk -> dealt:
+// 5000 chunks 89 -> 76 us (4 trials), 124 -> 105 (8), 195 -> 174 (16); 8000 chunks 102 ->
+// 93 (4), 224 -> 224 (16); S sampler, 33 000 chunks 201 -> 211 (2), 488 -> 598 (16).
+constexpr int64_t kDealtChunks = 8192;
+
+// The emitted trials of a round of explicit chunks, listed by their waves: a photon's
+// slot is known only when the block's waves have finished the round.
+template <int CAP>
+struct PhotonList {
+    float x[kWaves][CAP];           // what the draw needs (listed_s), then the energy
+    float frac[kWaves][CAP];        // share of the weight (SR_DN_WEIGHT only)
+    uint16_t meta[kWaves][CAP];     // lane, trial << 6
+    uint16_t next[kWaves][CAP];     // the same lane's next entry
+};
+
 // LDS of the kernel.  With the MLP sampler: the network and, per wave, the
 // compacted inputs of the emitted trials, which the ledger reduction reuses
 // after the last round.
-template <int KMAX, int SAMPLER, bool BOX = false>
+template <int KMAX, int SAMPLER, int MODE>
 struct alignas(16) StepSmem {
     union {
         struct {
@@ -294,61 +319,78 @@ struct alignas(16) StepSmem {
 };
 // Photons staged in LDS for one block-wide flush: wave w's first kStage photons
 // of its (single) round sit at [w][0, kStage).
-constexpr int kStage = 64;
+template <int KMAX>
+constexpr int kStage = KMAX >= 4 ? 64 : 48;     // with 48, eight blocks' LDS in a compute unit
+template <int KMAX>
 struct PhotonStage {
-    float eps[kWaves][kStage], w[kWaves][kStage];
-    float dir[3][kWaves][kStage], pos[3][kWaves][kStage];
-    uint32_t parent[kWaves][kStage], k[kWaves][kStage];
+    float eps[kWaves][kStage<KMAX>], w[kWaves][kStage<KMAX>];
+    float dir[3][kWaves][kStage<KMAX>], pos[3][kWaves][kStage<KMAX>];
+    uint32_t parent[kWaves][kStage<KMAX>], k[kWaves][kStage<KMAX>];
     uint32_t cnt[kWaves];       // staged photons per wave
     uint32_t base[kWaves];      // first buffer slot of each wave's chunk segment
 };
 // With four or more trials the proposal sampler also keeps the hot pieces of
-// the trial-density table in LDS (31.3 KB in all: five 256-thread blocks per
-// compute unit), and the quantum sampler those of its kernel table (29.3 KB);
-// with fewer trials the table lookups are too few to pay for the copy.
+// the trial-density table in LDS, and the quantum sampler those of its kernel
+// table; with fewer trials the table lookups are too few to pay for the copy.
+// (They share it with the ledger: 22.6 KB in all, seven 256-thread blocks per
+// compute unit.)
 template <int KMAX>
 constexpr bool kHotTable = KMAX >= 4;
-template <int KMAX>
-struct StepSmem<KMAX, SR_SAMPLER_S, false> {
-    LedgerSmem led;
-    PhotonStage stage;
-    float4 ghot[kHotTable<KMAX> ? kGHot : 1];
-};
-template <int KMAX>
-struct StepSmem<KMAX, SR_SAMPLER_TABLE, false> {
-    LedgerSmem led;
-    PhotonStage stage;
-};
-template <int KMAX>
-struct StepSmem<KMAX, SR_SAMPLER_QUANTUM, false> {
-    LedgerSmem led;
-    PhotonStage stage;
-    float4 qhot[kHotTable<KMAX> ? kQHot : 1];   // 29.3 KB in all
-};
 // With the LDS field box (SR_GATHER_BOX) the box shares its LDS with the
 // ledger and the photon stage: it is read only before either is written.
 // 32 352 bytes in all keeps five 256-thread blocks per compute unit.
 struct BoxReduce {
     int mn[kWaves][3], mx[kWaves][3];
 };
-struct alignas(16) BoxSmem {
+// HOT: float4 entries of the sampler's hot pieces, which are dead when the ledger is
+// written (uniform chunks).
+template <int KMAX, int MODE, int HOT>
+struct alignas(16) RoundSmem {
     union {
-        struct {
-            LedgerSmem led;
-            PhotonStage stage;
-        };
+        LedgerSmem led;
+        float4 hot[HOT];
+    };
+    PhotonStage<KMAX> stage;
+};
+template <int KMAX, int HOT>
+struct alignas(16) RoundSmem<KMAX, kRagged, HOT> {
+    LedgerSmem led;
+    PhotonList<64 * KMAX> list;
+    float4 hot[HOT];
+};
+template <int KMAX, int HOT>
+struct alignas(16) RoundSmem<KMAX, kLoop, HOT> {
+    LedgerSmem led;
+    float4 hot[HOT];
+};
+template <int KMAX, int HOT>
+struct alignas(16) RoundSmem<KMAX, kBox, HOT> {
+    union {
+        RoundSmem<KMAX, kUniform, 1> round;
         float box[6][kBoxCells];
     };
     BoxReduce red;
 };
-template <int KMAX>
-struct StepSmem<KMAX, SR_SAMPLER_S, true> : BoxSmem {};
-template <int KMAX>
-struct StepSmem<KMAX, SR_SAMPLER_TABLE, true> : BoxSmem {};
-template <int KMAX>
-struct StepSmem<KMAX, SR_SAMPLER_QUANTUM, true> : BoxSmem {};
-template <typename S>
-__device__ __forceinline__ LedgerSmem &ledger_smem(S &s) { return s.led; }
+template <int KMAX, int MODE>
+struct StepSmem<KMAX, SR_SAMPLER_S, MODE> : RoundSmem<KMAX, MODE, kHotTable<KMAX> ? kGHot : 1> {};
+template <int KMAX, int MODE>
+struct StepSmem<KMAX, SR_SAMPLER_TABLE, MODE> : RoundSmem<KMAX, MODE, 1> {};
+template <int KMAX, int MODE>
+struct StepSmem<KMAX, SR_SAMPLER_QUANTUM, MODE> : RoundSmem<KMAX, MODE, kHotTable<KMAX> ? kQHot : 1> {};
+template <bool BOX, typename S>
+__device__ __forceinline__ auto &round_smem(S &s) {
+    if constexpr (BOX) return s.round;
+    else return s;
+}
+
+// x of a listed trial: the S sampler lists R' itself (positive) or log2(1 - R')
+// (negative or zero), which is what trial_x starts from.
+__device__ __forceinline__ float listed_s(float rp, float lg, bool lower) { return lower ? rp : lg; }
+__device__ __forceinline__ float listed_x(float y) {
+    const float s = __builtin_amdgcn_sqrtf(y);
+    const float lo = s * __builtin_amdgcn_sqrtf(s);
+    return y > 0.0f ? lo : fmaf(-0.69314718055994531f, y, -0.25131442828090605f);
+}
 
 // Field box of a block (3D, uniform chunks, called by every thread of the
 // block): the nodes of every stencil of the block's particles, from the
@@ -359,22 +401,23 @@ __device__ __forceinline__ LedgerSmem &ledger_smem(S &s) { return s.led; }
 // components are copied into LDS with coalesced loads (the caller syncs
 // before reading them).
 template <typename R>
-__device__ __forceinline__ bool load_field_box(const StepArgs<R> &a, BoxSmem &sm, bool act,
+__device__ __forceinline__ bool load_field_box(const StepArgs<R> &a, BoxReduce &red,
+                                               float (*box)[kBoxCells], bool act,
                                                const int cell[3], FieldBox &fb) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
         const int lo = wave_min_i(act ? cell[q] : 0x7fffffff);
         const int hi = wave_max_i(act ? cell[q] : -0x7fffffff);
-        if (lane == 0) { sm.red.mn[wave][q] = lo; sm.red.mx[wave][q] = hi; }
+        if (lane == 0) { red.mn[wave][q] = lo; red.mx[wave][q] = hi; }
     }
     __syncthreads();
     int cells = 1;
     bool ok = true;
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-        const int lo = min(min(sm.red.mn[0][q], sm.red.mn[1][q]), min(sm.red.mn[2][q], sm.red.mn[3][q]));
-        const int hi = max(max(sm.red.mx[0][q], sm.red.mx[1][q]), max(sm.red.mx[2][q], sm.red.mx[3][q]));
+        const int lo = min(min(red.mn[0][q], red.mn[1][q]), min(red.mn[2][q], red.mn[3][q]));
+        const int hi = max(max(red.mx[0][q], red.mx[1][q]), max(red.mx[2][q], red.mx[3][q]));
         const int n = a.g.n[q];
         const int ext = hi - lo + 3;
         ok = ok && hi >= lo && ext < n;
@@ -403,33 +446,50 @@ __device__ __forceinline__ bool load_field_box(const StepArgs<R> &a, BoxSmem &sm
 #pragma unroll
         for (int c = 0; c < 6; ++c) v[c] = ld(a.f[c], off);
 #pragma unroll
-        for (int c = 0; c < 6; ++c) sm.box[c][e] = v[c];
+        for (int c = 0; c < 6; ++c) box[c][e] = v[c];
     }
     return true;
 }
 
-// Occupancy target: the FP32 3D kernels with 4 to 8 trials sit a couple of
-// VGPRs above the 96 that five waves per SIMD allow; asking for five costs no
-// spills and gives them a fifth wave.  The learned sampler's come to 156 with 8
-// trials; four waves (128 VGPRs, and the 34 KB of LDS allow four blocks per CU)
-// took the step of 2^20 electrons from 159 to 152 us.
-template <typename R, int DIM, int KMAX, int SAMPLER>
+// Occupancy target.  With a single round the kernels need 73 VGPRs in 3D (49 in 2D): six
+// waves per SIMD, where the loop over rounds took 96 and five; asking for seven (72) gives
+// the same time, the gather's addresser being what bounds them (step of 2^24 electrons, 8
+// trials: 1224 us with the loop, 1192 without, 1196 with seven waves).  The loop with 4 to 8
+// trials sits a couple of VGPRs above the 96 that five waves allow; asking for five costs
+// no spills there.  Dealt rounds come to 111 and spill if asked for five.  The learned
+// sampler's come to 156 with 8 trials; four waves (128 VGPRs, and the 34 KB of LDS allow
+// four blocks per CU) took the step of 2^20 electrons from 159 to 152 us.
+template <typename R, int DIM, int KMAX, int SAMPLER, int MODE>
 constexpr int step_waves_per_eu() {
-    if (sizeof(R) == 4 && SAMPLER == SR_SAMPLER_MLP && KMAX >= 4 && KMAX <= 8) return 4;
-    return (sizeof(R) == 4 && DIM == 3 && KMAX >= 4 && KMAX <= 8 && SAMPLER != SR_SAMPLER_MLP) ? 5
-                                                                                              : 1;
+    if (sizeof(R) != 4) return 1;
+    if (SAMPLER == SR_SAMPLER_MLP) return KMAX >= 4 && KMAX <= 8 ? 4 : 1;
+    if (MODE == kRagged) return KMAX <= 4 ? 4 : 1;
+    if (MODE == kBox) return 5;         // what its LDS allows
+    if (MODE == kLoop) return DIM == 3 && KMAX >= 4 && KMAX <= 8 ? 5 : 1;
+    return DIM == 3 && KMAX <= 8 ? 6 : 1;
 }
+
+// The FP64 path has no sort: the more of its waves gather at once, the less of what they
+// fetch is read again (2^20 electrons on 192x192x96: 474 us with four waves per SIMD, 475.5
+// with the five that its 90 VGPRs allow).
+template <typename R>
+constexpr int step_waves_max() { return sizeof(R) == 4 ? 8 : 4; }
 
 // FLOOR: the grid-frequency floor is on (a.e_grid > 0); a template flag, so the
 // kernels without it carry none of its code.
 // BOX: the SR_GATHER_BOX gather (3D, uniform chunks, proposal, table or
 // quantum sampler); the host launches it only there.
-template <typename R, int DIM, int KMAX, int SAMPLER, bool FLOOR, bool BOX>
+template <typename R, int DIM, int KMAX, int SAMPLER, bool FLOOR, int MODE>
 __global__ __launch_bounds__(kBlock)
-__attribute__((amdgpu_waves_per_eu(step_waves_per_eu<R, DIM, KMAX, SAMPLER>())))
+__attribute__((amdgpu_waves_per_eu(step_waves_per_eu<R, DIM, KMAX, SAMPLER, MODE>(),
+                                   step_waves_max<R>())))
 void push_emit_kernel(const StepArgs<R> a) {
+    constexpr bool BOX = MODE == kBox;
+    constexpr bool kRag = MODE == kRagged;
+    constexpr bool kSingle = MODE == kUniform || MODE == kBox;
     static_assert(!BOX || (DIM == 3 && SAMPLER != SR_SAMPLER_MLP), "the field box is 3D");
-    __shared__ StepSmem<KMAX, SAMPLER, BOX> sm;
+    static_assert(!kRag || SAMPLER != SR_SAMPLER_MLP, "explicit chunks, one wave each");
+    __shared__ StepSmem<KMAX, SAMPLER, MODE> sm;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if constexpr (SAMPLER == SR_SAMPLER_MLP) {
@@ -443,11 +503,11 @@ void push_emit_kernel(const StepArgs<R> a) {
         }
     }
     if constexpr (SAMPLER == SR_SAMPLER_S && !BOX && kHotTable<KMAX>) {
-        for (int e = tid; e < kGHot; e += kBlock) sm.ghot[e] = a.tab.gtab[ghot_source(e)];
+        for (int e = tid; e < kGHot; e += kBlock) sm.hot[e] = a.tab.gtab[ghot_source(e)];
         __syncthreads();
     }
     if constexpr (SAMPLER == SR_SAMPLER_QUANTUM && !BOX && kHotTable<KMAX>) {
-        for (int e = tid; e < kQHot; e += kBlock) sm.qhot[e] = a.tab.qtab[2 * kQHot0 + e];
+        for (int e = tid; e < kQHot; e += kBlock) sm.hot[e] = a.tab.qtab[2 * kQHot0 + e];
         __syncthreads();
     }
     // one chunk per wave, kWaves consecutive chunks per block (blocks mapped so
@@ -462,40 +522,71 @@ void push_emit_kernel(const StepArgs<R> a) {
         e0 = a.start ? (uint32_t)a.start[c + 1] : min(s0 + (uint32_t)kChunk, (uint32_t)a.n);
     }
     const uint32_t pp = (uint32_t)a.per_particle;
-    const uint32_t seg_base = s0 * pp;
-    const uint32_t seg_cap = (e0 - s0) * pp;
-    // With uniform chunks every wave has a single round, so the S and table
-    // samplers stage their photons in LDS and the block writes them together
-    // at the end (one store per array for up to 256 photons of four chunks).
-    constexpr bool kCanStage = SAMPLER != SR_SAMPLER_MLP;
-    const bool staged = kCanStage && a.start == nullptr;
+    uint32_t seg_base = s0 * pp;
+    uint32_t seg_cap = (e0 - s0) * pp;
+    // Uniform chunks: a single round a wave.  With few trials the photons are staged in
+    // LDS and the block writes them together at the end (one store per array for up to
+    // 256 photons of four chunks).
+    constexpr bool kCanStage = SAMPLER != SR_SAMPLER_MLP && kSingle;
+    // Explicit chunks: the block's rounds, in the order of its chunks, are dealt to its
+    // waves in turn, so that a chunk of many rounds is not one wave's chain (300 007
+    // particles in 5000 chunks of 60 on average: the longest has 9 rounds).
+    uint32_t first[kWaves + 1], round0[kWaves + 1], run[kWaves];   // chunk bounds, rounds, photons
+    uint32_t rounds = 0;
+    if constexpr (kRag) {
+#pragma unroll
+        for (int j = 0; j <= kWaves; ++j)
+            first[j] = (uint32_t)__builtin_amdgcn_readfirstlane(
+                (int)a.start[min((int64_t)(blk * kWaves + j), a.n_chunks)]);
+#pragma unroll
+        for (int j = 0; j < kWaves; ++j) {
+            round0[j] = rounds;
+            rounds += (first[j + 1] - first[j] + kChunk - 1) / kChunk;
+            run[j] = 0;
+        }
+        round0[kWaves] = rounds;
+    }
     const int K = a.K;
     const float invK = 1.0f / (float)K;
 
-    // Ledger sums of the lane.  With the proposal and table samplers each
-    // round's sums are added to the lane's own LDS ledger slot at the end of
-    // the round, so no FP64 sum stays in registers across rounds (it would
-    // hold VGPRs through the next round's gather and cost a wave per SIMD);
-    // the learned sampler shares that LDS with the network and keeps them in
-    // registers.
-    constexpr bool kLdsAcc = SAMPLER != SR_SAMPLER_MLP;
-    double tot_emit = 0.0, tot_ll = 0.0, tot_de = 0.0, tot_clamp = 0.0, tot_drop = 0.0;
-    float tot_w = 0.0f;
-    if constexpr (kLdsAcc && !BOX) {
-        LedgerSmem &rs = ledger_smem(sm);
+    // Ledger sums of the lane; one wave a chunk adds each round's to the lane's own LDS slot
+    // instead (held in registers through the next round's gather, they cost a wave per SIMD).
+    constexpr bool kLdsAcc = MODE == kLoop && SAMPLER != SR_SAMPLER_MLP;
+    if constexpr (kLdsAcc) {
+        LedgerSmem &rs = sm.led;
 #pragma unroll
         for (int q = 0; q < 5; ++q) rs.d[q][tid] = 0.0;
         rs.f[0][tid] = 0.0f;
     }
+    double tot_emit = 0.0, tot_ll = 0.0, tot_de = 0.0, tot_clamp = 0.0, tot_drop = 0.0;
+    float tot_w = 0.0f;
     float chi_max = 0.0f;
     uint32_t flags = 0;
     uint32_t run_base = 0;
     bool box_used = false;
 
-    // BOX (uniform chunks): exactly one round per wave, waves without a chunk
-    // running it with no active lane, so the block-wide steps of the field box
-    // are reached by every thread
-    for (uint32_t base = s0; BOX ? base == s0 : base < e0; base += kChunk) {
+    // uniform chunks: exactly one round per wave, waves without a chunk running it with no active lane,
+    // so the block-wide steps of the field box are reached by every thread
+    uint32_t batch = 0;      // explicit chunks: first round of the waves' four
+    for (uint32_t base = s0; kRag ? batch < rounds : kSingle ? base == s0 : base < e0;
+         base += kChunk, batch += kWaves) {
+        uint32_t mine = 0;   // the round's chunk in the block
+        if constexpr (kRag) {
+            const uint32_t r = batch + (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+            const bool on = r < rounds;
+#pragma unroll
+            for (int j = 1; j < kWaves; ++j) mine += r >= round0[j] ? 1u : 0u;
+            base = 0;
+            e0 = 0;
+#pragma unroll
+            for (int j = 0; j < kWaves; ++j)
+                if (on && mine == (uint32_t)j) {
+                    base = first[j] + (r - round0[j]) * kChunk;
+                    e0 = first[j + 1];
+                    seg_base = first[j] * pp;
+                    seg_cap = (e0 - first[j]) * pp;
+                }
+        }
         double acc_emit = 0.0, acc_ll = 0.0, acc_de = 0.0, acc_clamp = 0.0, acc_drop = 0.0;
         float acc_w = 0.0f;
         const uint32_t i = base + lane;
@@ -520,7 +611,7 @@ void push_emit_kernel(const StepArgs<R> a) {
                 setup_axis<R>(a.g, 2, pos[2], Z);
                 cell[0] = X.i0; cell[1] = Y.i0; cell[2] = Z.i0;
             }
-            use_box = load_field_box<R>(a, sm, active, cell, fb);
+            use_box = load_field_box<R>(a, sm.red, sm.box, active, cell, fb);
             if (use_box) __syncthreads();
             box_used = use_box;
         }
@@ -564,10 +655,6 @@ void push_emit_kernel(const StepArgs<R> a) {
         }
         if constexpr (BOX) {
             if (use_box) __syncthreads();          // every wave is done with the box
-            LedgerSmem &rs = ledger_smem(sm);
-#pragma unroll
-            for (int q = 0; q < 5; ++q) rs.d[q][tid] = 0.0;
-            rs.f[0][tid] = 0.0f;
         }
 
         // ---- K trials.  Inactive lanes take part in the wave-wide steps with a
@@ -575,9 +662,81 @@ void push_emit_kernel(const StepArgs<R> a) {
         // lane prefix (mbcnt); the chunk's segment belongs to this wave alone.
         float delta_ph = 0.0f;                 // sum over trials of frac * eps
         uint32_t wave_tot = 0;
+        // the list: entries, and the lane's first, last and number of them
+        uint32_t listed = 0, l_first = 0, l_last = 0, l_mine = 0;
+        const bool weighted = a.dn_policy == SR_DN_WEIGHT;
         float2 rr = make_float2(1.0f, 0.0f);
         if (SAMPLER != SR_SAMPLER_S && SAMPLER != SR_SAMPLER_QUANTUM && active && a.kin_cut)
             rr = r_lookup(a.tab.r, chif);
+        // f(entry, its share of the weight, its energy) for the lane's entries, in order
+        const auto each_mine = [&](auto &&f) {
+            if constexpr (kRag) {
+                auto &L = round_smem<BOX>(sm).list;
+                uint32_t at = l_first;
+                for (uint32_t q = 0; q < l_mine; ++q) {
+                    f(at, weighted ? L.frac[wave][at] : invK, L.x[wave][at]);
+                    at = L.next[wave][at];
+                }
+            }
+        };
+        // energies of the listed photons, and their records from slot `slot0` on
+        const auto list_energies = [&]() {
+            if constexpr (kRag) {
+                auto &L = round_smem<BOX>(sm).list;
+                wave_lds_sync();
+                for (uint32_t t = 0; t < listed; t += 64) {
+                    const uint32_t e = min(t + (uint32_t)lane, listed - 1u);
+                    const uint32_t meta = L.meta[wave][e];
+                    const int from = (int)(meta & 63u) << 2;
+                    const auto get = [&](float v) {
+                        return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
+                    };
+                    const float y = L.x[wave][e];
+                    float x = y;
+                    if (SAMPLER == SR_SAMPLER_S) x = listed_x(y);
+                    if (SAMPLER == SR_SAMPLER_TABLE && !FLOOR) {
+                        float lnU, ln1mU;
+                        direct_u(__float_as_uint(y), make_float2(get(rr.x), get(rr.y)), lnU, ln1mU);
+                        x = __builtin_amdgcn_exp2f(t1_log2x(a.tab.t1, lnU, ln1mU));
+                    }
+                    const float eps = get(eps_unit) * x;
+                    if (t + (uint32_t)lane < listed) L.x[wave][e] = eps;
+                }
+                wave_lds_sync();
+            }
+        };
+        const auto list_store = [&](uint32_t slot0) {
+            if constexpr (kRag) {
+                auto &L = round_smem<BOX>(sm).list;
+                const PhotonOut P = cold_args<R>();
+                for (uint32_t t = 0; t < listed; t += 64) {
+                    const uint32_t e = min(t + (uint32_t)lane, listed - 1u);
+                    const uint32_t meta = L.meta[wave][e];
+                    const int from = (int)(meta & 63u) << 2;
+                    const auto get = [&](float v) {
+                        return __int_as_float(__builtin_amdgcn_ds_bpermute(from, __float_as_int(v)));
+                    };
+                    const float wph = get(wi_f) * (weighted ? L.frac[wave][e] : invK);
+                    const float d[3] = {get(dirf[0]), get(dirf[1]), get(dirf[2])};
+                    const float ps[3] = {get(posf[0]), get(posf[1]), get(posf[2])};
+                    const uint32_t parent = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)pid);
+                    const uint32_t slot = slot0 + e;
+                    if (t + (uint32_t)lane < listed && slot < seg_cap)
+                        store_photon(P, seg_base + slot, L.x[wave][e], wph, d, ps, parent, meta >> 6,
+                                     a.step);
+                }
+            }
+        };
+        // photons past the segment's end
+        const auto list_dropped = [&](uint32_t slot0) {
+            if (slot0 + listed > seg_cap)
+                each_mine([&](uint32_t at, float frac, float eps) {
+                    if (slot0 + at < seg_cap) return;
+                    const float wph = wi_f * frac;
+                    acc_drop += (double)wph * (double)eps;
+                    flags |= SR_W_PHOTON_OVERFLOW;
+                });
+        };
         constexpr bool kProposal = SAMPLER == SR_SAMPLER_S || SAMPLER == SR_SAMPLER_QUANTUM;
         const float rate = !active ? 0.0f : (kProposal ? a.rate_c * Hf : a.direct_c * Hf * rr.x);
         if constexpr (SAMPLER != SR_SAMPLER_MLP) {
@@ -600,14 +759,14 @@ void push_emit_kernel(const StepArgs<R> a) {
                 bool lower = true;
                 if (SAMPLER == SR_SAMPLER_S) {
                     if constexpr (SAMPLER == SR_SAMPLER_S && !BOX && kHotTable<KMAX>)
-                        dn = rate * trial_q_hot(wa, a.tab.gtab, sm.ghot, a.tab.pa, lg, lower);
+                        dn = rate * trial_q_hot(wa, a.tab.gtab, sm.hot, a.tab.pa, lg, lower);
                     else
                         dn = rate * trial_q(wa, a.tab.gtab, a.tab.pa, lg, lower);
                     if (trial_is_cut(cut, lg, lower)) dn = 0.0f;
                     if (FLOOR && trial_is_floored(flr, lg, lower)) dn = 0.0f;
                 } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
                     if constexpr (SAMPLER == SR_SAMPLER_QUANTUM && !BOX && kHotTable<KMAX>)
-                        dn = rate * quantum_q_t<true>(wa, a.tab.qtab, sm.qhot, a.tab.pa, chif, xq);
+                        dn = rate * quantum_q_t<true>(wa, a.tab.qtab, sm.hot, a.tab.pa, chif, xq);
                     else
                         dn = rate * quantum_q(wa, a.tab.qtab, a.tab.pa, chif, xq);
                     if (FLOOR && eps_unit * xq < a.e_grid) dn = 0.0f;
@@ -634,7 +793,28 @@ void push_emit_kernel(const StepArgs<R> a) {
                     emit = eps_unit * x >= a.e_grid;
                 }
                 const uint64_t m = __ballot(emit);
-                if (m) {
+                if constexpr (kRag) {
+                    if (m) {
+                        if (emit) {
+                            auto &L = round_smem<BOX>(sm).list;
+                            const uint32_t e = listed + lane_prefix(m);
+                            float y;
+                            if (SAMPLER == SR_SAMPLER_S)
+                                y = listed_s((float)((wa >> 9) * 2u + 1u) * 0x1p-24f, lg, lower);
+                            else if (SAMPLER == SR_SAMPLER_QUANTUM) y = xq;
+                            else y = kDrawFirst ? x : __uint_as_float(wa);
+                            L.x[wave][e] = y;
+                            if (weighted) L.frac[wave][e] = frac;
+                            L.meta[wave][e] = (uint16_t)((uint32_t)lane | (uint32_t)k << 6);
+                            if (l_mine) L.next[wave][l_last] = (uint16_t)e;
+                            else l_first = e;
+                            l_last = e;
+                            ++l_mine;
+                        }
+                        listed = (uint32_t)__builtin_amdgcn_readfirstlane(
+                            (int)(listed + (uint32_t)__popcll(m)));
+                    }
+                } else if (m) {
                     if (emit) {
                         if (!kDrawFirst) x = draw_x();
                         const float eps = eps_unit * x;
@@ -642,8 +822,10 @@ void push_emit_kernel(const StepArgs<R> a) {
                         delta_ph += frac * eps;
                         const uint32_t slot = run_base + wave_tot + lane_prefix(m);
                         if (slot < seg_cap) {
-                            if (staged && slot < (uint32_t)kStage) {
-                                PhotonStage &S = sm.stage;
+                            bool kept = false;
+                            if constexpr (kCanStage) if (slot < (uint32_t)kStage<KMAX>) {
+                                PhotonStage<KMAX> &S = round_smem<BOX>(sm).stage;
+                                kept = true;
                                 S.eps[wave][slot] = eps;
                                 S.w[wave][slot] = wph;
                                 S.dir[0][wave][slot] = dirf[0];
@@ -654,7 +836,8 @@ void push_emit_kernel(const StepArgs<R> a) {
                                 S.pos[2][wave][slot] = posf[2];
                                 S.parent[wave][slot] = pid;
                                 S.k[wave][slot] = (uint32_t)k;
-                            } else {
+                            }
+                            if (!kept) {
                                 store_photon(cold_args<R>(), seg_base + slot, eps, wph, dirf, posf,
                                              pid, (uint32_t)k, a.step);
                             }
@@ -754,6 +937,10 @@ void push_emit_kernel(const StepArgs<R> a) {
             }
         }
 
+        if constexpr (kRag) {
+            list_energies();
+            each_mine([&](uint32_t, float frac, float eps) { delta_ph += frac * eps; });
+        }
         if (active) {
             acc_emit += (double)wi_f * (double)delta_ph;
             // Landau-Lifshitz loss of the step (eq:LLformOfRRForce)
@@ -798,8 +985,51 @@ void push_emit_kernel(const StepArgs<R> a) {
             acc_w += wi_f;
         }
         run_base += wave_tot;
-        if constexpr (kLdsAcc) {
-            LedgerSmem &rs = ledger_smem(sm);
+        if constexpr (kRag) {
+            // the waves' counts give each its first slot; then thread (j, lane) adds what
+            // lane `lane` of chunk j's rounds has, in their order
+            LedgerSmem &rs = round_smem<BOX>(sm).led;
+            rs.d[0][tid] = acc_emit;
+            rs.d[1][tid] = acc_ll;
+            rs.d[2][tid] = acc_de;
+            rs.d[3][tid] = acc_clamp;
+            rs.f[0][tid] = acc_w;
+            if (lane == 0) rs.cnt[wave] = listed;
+            __syncthreads();
+            uint32_t slot0 = 0;
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t r = batch + w, n = rs.cnt[w];
+#pragma unroll
+                for (int j = 0; j < kWaves; ++j) {
+                    if (r < round0[j] || r >= round0[j + 1]) continue;
+                    if (w == wave) slot0 = run[j];
+                    run[j] += n;
+                }
+            }
+            list_store(slot0);
+            list_dropped(slot0);
+            rs.d[4][tid] = acc_drop;
+            __syncthreads();
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                const uint32_t r = batch + w;
+                uint32_t lo = 0, hi = 0;
+#pragma unroll
+                for (int j = 0; j < kWaves; ++j)
+                    if (j == wave) { lo = round0[j]; hi = round0[j + 1]; }
+                if (r < lo || r >= hi) continue;
+                const int t = w * 64 + lane;
+                tot_emit += rs.d[0][t];
+                tot_ll += rs.d[1][t];
+                tot_de += rs.d[2][t];
+                tot_clamp += rs.d[3][t];
+                tot_drop += rs.d[4][t];
+                tot_w += rs.f[0][t];
+            }
+            __syncthreads();
+        } else if constexpr (kLdsAcc) {
+            LedgerSmem &rs = sm.led;
             rs.d[0][tid] += acc_emit;
             rs.d[1][tid] += acc_ll;
             rs.d[2][tid] += acc_de;
@@ -814,6 +1044,12 @@ void push_emit_kernel(const StepArgs<R> a) {
             tot_drop += acc_drop;
             tot_w += acc_w;
         }
+    }
+    if constexpr (kRag) {
+        run_base = 0;
+#pragma unroll
+        for (int j = 0; j < kWaves; ++j)
+            if (j == wave) run_base = run[j];
     }
 
     if (have && lane == 0) cold_args<R>().seg_count[c] = run_base;
@@ -832,9 +1068,10 @@ void push_emit_kernel(const StepArgs<R> a) {
     // whole block (four values per lane, then one wave reduction), so the block
     // pays for each column's wave reduction once.  Clamped and dropped energy
     // are rare: reduced only when some lane has them.
-    if constexpr (SAMPLER == SR_SAMPLER_MLP) __syncthreads();   // LDS shared with the sampler
-    LedgerSmem &rs = ledger_smem(sm);
+    LedgerSmem &rs = round_smem<BOX>(sm).led;
     if constexpr (!kLdsAcc) {
+        // LDS shared with the sampler
+        if constexpr (SAMPLER == SR_SAMPLER_MLP || (MODE == kUniform && kHotTable<KMAX>)) __syncthreads();
         rs.d[0][tid] = tot_emit;
         rs.d[1][tid] = tot_ll;
         rs.d[2][tid] = tot_de;
@@ -848,26 +1085,25 @@ void push_emit_kernel(const StepArgs<R> a) {
         rs.flags[wave] = wf;
     }
     if constexpr (kCanStage) {
-        if (staged && lane == 0) {
-            sm.stage.cnt[wave] = min(min(run_base, seg_cap), (uint32_t)kStage);
-            sm.stage.base[wave] = seg_base;
+        PhotonStage<KMAX> &S = round_smem<BOX>(sm).stage;
+        if (lane == 0) {
+            S.cnt[wave] = min(min(run_base, seg_cap), (uint32_t)kStage<KMAX>);
+            S.base[wave] = seg_base;
         }
     }
     __syncthreads();
     if constexpr (kCanStage) {
-        if (staged) {
-            const PhotonStage &S = sm.stage;
-            const uint32_t c0 = S.cnt[0], c1 = c0 + S.cnt[1], c2 = c1 + S.cnt[2];
-            const uint32_t total = c2 + S.cnt[3];
-            const uint32_t e = (uint32_t)tid;
-            if (e < total) {
-                const int wv = (int)(e >= c0) + (int)(e >= c1) + (int)(e >= c2);
-                const uint32_t j = e - (wv == 0 ? 0u : wv == 1 ? c0 : wv == 2 ? c1 : c2);
-                const float d[3] = {S.dir[0][wv][j], S.dir[1][wv][j], S.dir[2][wv][j]};
-                const float ps[3] = {S.pos[0][wv][j], S.pos[1][wv][j], S.pos[2][wv][j]};
-                store_photon(cold_args<R>(), S.base[wv] + j, S.eps[wv][j], S.w[wv][j], d, ps,
-                             S.parent[wv][j], S.k[wv][j], a.step);
-            }
+        const PhotonStage<KMAX> &S = round_smem<BOX>(sm).stage;
+        const uint32_t c0 = S.cnt[0], c1 = c0 + S.cnt[1], c2 = c1 + S.cnt[2];
+        const uint32_t total = c2 + S.cnt[3];
+        const uint32_t e = (uint32_t)tid;
+        if (e < total) {
+            const int wv = (int)(e >= c0) + (int)(e >= c1) + (int)(e >= c2);
+            const uint32_t j = e - (wv == 0 ? 0u : wv == 1 ? c0 : wv == 2 ? c1 : c2);
+            const float d[3] = {S.dir[0][wv][j], S.dir[1][wv][j], S.dir[2][wv][j]};
+            const float ps[3] = {S.pos[0][wv][j], S.pos[1][wv][j], S.pos[2][wv][j]};
+            store_photon(cold_args<R>(), S.base[wv] + j, S.eps[wv][j], S.w[wv][j], d, ps,
+                         S.parent[wv][j], S.k[wv][j], a.step);
         }
     }
     double *row = cold_args<R>().partials + (size_t)blk * kPartCols;
@@ -1534,8 +1770,10 @@ int launch_step(PARTS *parts, const sr_fields_f32 *fields, const sr_grid *grid, 
 
     // with events: the dispatch packet itself records the kernel's start and stop
     // the field-box gather: FP32 path, 3D, uniform chunks, not the learned sampler
-    constexpr bool kBoxR = std::is_same<R, float>::value;
-    const bool box = prm->gather == SR_GATHER_BOX && dim == 3 && chunks->start == nullptr &&
+    constexpr bool kFloat = std::is_same<R, float>::value;
+    const bool ragged = chunks->start != nullptr;
+    const bool dealt = n_chunks <= kDealtChunks;
+    const bool box = prm->gather == SR_GATHER_BOX && dim == 3 && !ragged &&
                      prm->sampler != SR_SAMPLER_MLP;
 #define SR_LAUNCH(DIMV, KMV, SMP, FL, BX)                                                      \
     if (ev_start || ev_stop)                                                                   \
@@ -1551,24 +1789,32 @@ int launch_step(PARTS *parts, const sr_fields_f32 *fields, const sr_grid *grid, 
         case 8: SR_LAUNCH(DIMV, 8, SMP, FL, BX); break;    \
         default: SR_LAUNCH(DIMV, 16, SMP, FL, BX); break;  \
     }
-#define SR_BY_DIM(SMP, FL, BOXOK)                                      \
-    switch (dim) {                                                     \
-        case 0: SR_BY_K(0, SMP, FL, false); break;                     \
-        case 2: SR_BY_K(2, SMP, FL, false); break;                     \
-        default:                                                       \
-            if (box) { SR_BY_K(3, SMP, FL, (BOXOK && kBoxR)); }        \
-            else { SR_BY_K(3, SMP, FL, false); }                       \
-            break;                                                     \
+#define SR_BY_CHUNKS(DIMV, SMP, FL, MLP)                                                \
+    if (!ragged) { SR_BY_K(DIMV, SMP, FL, kUniform); }                                  \
+    else if (dealt) { SR_BY_K(DIMV, SMP, FL, (!MLP && kFloat ? kRagged : kLoop)); }     \
+    else { SR_BY_K(DIMV, SMP, FL, kLoop); }
+#define SR_BY_DIM(SMP, FL, MLP)                                                         \
+    switch (dim) {                                                                      \
+        case 0:                                                                         \
+            if (ragged) { SR_BY_K(0, SMP, FL, kLoop); }                                 \
+            else { SR_BY_K(0, SMP, FL, kUniform); }                                     \
+            break;                                                                      \
+        case 2: SR_BY_CHUNKS(2, SMP, FL, MLP) break;                                    \
+        default:                                                                        \
+            if (box) { SR_BY_K(3, SMP, FL, (!MLP && kFloat ? kBox : kUniform)); }       \
+            else { SR_BY_CHUNKS(3, SMP, FL, MLP) }                                      \
+            break;                                                                      \
     }
 #define SR_BY_FLOOR(SMP)                                     \
-    if (a.e_grid > 0.0f) { SR_BY_DIM(SMP, true, true); }     \
-    else { SR_BY_DIM(SMP, false, true); }
+    if (a.e_grid > 0.0f) { SR_BY_DIM(SMP, true, false); }    \
+    else { SR_BY_DIM(SMP, false, false); }
     if (prm->sampler == SR_SAMPLER_S) { SR_BY_FLOOR(SR_SAMPLER_S); }
     else if (prm->sampler == SR_SAMPLER_TABLE) { SR_BY_FLOOR(SR_SAMPLER_TABLE); }
     else if (prm->sampler == SR_SAMPLER_QUANTUM) { SR_BY_FLOOR(SR_SAMPLER_QUANTUM); }
-    else { SR_BY_DIM(SR_SAMPLER_MLP, false, false); }
+    else { SR_BY_DIM(SR_SAMPLER_MLP, false, true); }
 #undef SR_BY_FLOOR
 #undef SR_BY_DIM
+#undef SR_BY_CHUNKS
 #undef SR_BY_K
 #undef SR_LAUNCH
     SR_HIP_CHECK(hipGetLastError());
