@@ -20,7 +20,11 @@ def _ptr(t):
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the current device's current stream, as torch.cuda.current_stream() gives it, without
+    # building a Stream object (2.9 us of a small call's 15)
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
 
 
 def lib():
