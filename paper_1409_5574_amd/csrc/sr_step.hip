@@ -451,10 +451,12 @@ __device__ __forceinline__ bool load_field_box(const StepArgs<R> &a, BoxReduce &
     return true;
 }
 
-// Occupancy target.  With a single round the kernels need 73 VGPRs in 3D (49 in 2D): six
-// waves per SIMD, where the loop over rounds took 96 and five; asking for seven (72) gives
-// the same time, the gather's addresser being what bounds them (step of 2^24 electrons, 8
-// trials: 1224 us with the loop, 1192 without, 1196 with seven waves).  The loop with 4 to 8
+// Occupancy target: five waves per SIMD for the FP32 3D kernels.  With a single round they
+// need 73 VGPRs and could run six; that is 1% faster where a block's particles are close
+// together (2^24 electrons at half an electron per cell, 8 trials: 1289 us, 1300 with five,
+// 1313 with the loop over rounds, which took 96 VGPRs), but the more waves gather at once,
+// the less of what they fetch is read again: at an eighth per cell, K = 1 and a sort every
+// ten steps 2054 us with six, 2039 with five.  The loop over a chunk's rounds with 4 to 8
 // trials sits a couple of VGPRs above the 96 that five waves allow; asking for five costs
 // no spills there.  Dealt rounds come to 111 and spill if asked for five.  The learned
 // sampler's come to 156 with 8 trials; four waves (128 VGPRs, and the 34 KB of LDS allow
@@ -464,16 +466,14 @@ constexpr int step_waves_per_eu() {
     if (sizeof(R) != 4) return 1;
     if (SAMPLER == SR_SAMPLER_MLP) return KMAX >= 4 && KMAX <= 8 ? 4 : 1;
     if (MODE == kRagged) return KMAX <= 4 ? 4 : 1;
-    if (MODE == kBox) return 5;         // what its LDS allows
     if (MODE == kLoop) return DIM == 3 && KMAX >= 4 && KMAX <= 8 ? 5 : 1;
-    return DIM == 3 && KMAX <= 8 ? 6 : 1;
+    return DIM == 3 && KMAX <= 8 ? 5 : 1;
 }
 
-// The FP64 path has no sort: the more of its waves gather at once, the less of what they
-// fetch is read again (2^20 electrons on 192x192x96: 474 us with four waves per SIMD, 475.5
+// At most; the FP64 path has no sort (2^20 electrons on 192x192x96: 474 us with four waves per SIMD, 475.5
 // with the five that its 90 VGPRs allow).
-template <typename R>
-constexpr int step_waves_max() { return sizeof(R) == 4 ? 8 : 4; }
+template <typename R, int DIM>
+constexpr int step_waves_max() { return sizeof(R) != 4 ? 4 : DIM == 3 ? 5 : 8; }
 
 // FLOOR: the grid-frequency floor is on (a.e_grid > 0); a template flag, so the
 // kernels without it carry none of its code.
@@ -482,7 +482,7 @@ constexpr int step_waves_max() { return sizeof(R) == 4 ? 8 : 4; }
 template <typename R, int DIM, int KMAX, int SAMPLER, bool FLOOR, int MODE>
 __global__ __launch_bounds__(kBlock)
 __attribute__((amdgpu_waves_per_eu(step_waves_per_eu<R, DIM, KMAX, SAMPLER, MODE>(),
-                                   step_waves_max<R>())))
+                                   step_waves_max<R, DIM>())))
 void push_emit_kernel(const StepArgs<R> a) {
     constexpr bool BOX = MODE == kBox;
     constexpr bool kRag = MODE == kRagged;
