@@ -541,7 +541,8 @@ void push_emit_kernel(const StepArgs<R> a) {
 #pragma unroll
         for (int j = 0; j < kWaves; ++j) {
             round0[j] = rounds;
-            rounds += (first[j + 1] - first[j] + kChunk - 1) / kChunk;
+            // (bounds that decrease hold no particle)
+            rounds += first[j + 1] > first[j] ? (first[j + 1] - first[j] + kChunk - 1) / kChunk : 0u;
             run[j] = 0;
         }
         round0[kWaves] = rounds;
