@@ -184,9 +184,11 @@ __device__ __forceinline__ int unwrap_cell(int i, int ref, int n) {
 // far since the last sort) is taken in up to kDepSlabs slabs along its widest axis,
 // each particle in the slab of its cell, with the LDS of one: that costs the slabs'
 // common nodes twice, where a particle outside the box adds to the grid by itself.
-// A box too large for that (an unsorted ensemble) shrinks, widest axis first, to a
-// window of at most `cap` nodes about the block's mean cell; the particles whose
-// nodes leave the window add to the grid directly.
+// Slabs are taken one after another, so a launch whose blocks do not fill the chip is
+// allowed fewer (max_slabs).  A box too large for its slabs (an unsorted ensemble) is
+// none (false), or with WINDOW shrinks, widest axis first, to a window of at most `cap`
+// nodes about the block's mean cell; the particles whose nodes leave the window add to
+// the grid directly.
 struct DepShared {
     int ref[3], lo[3], hi[3];   // first particle's cell; smallest and largest unwrapped cells
     uint32_t bmax;              // largest bound, as bits (no bound is negative)
@@ -198,7 +200,7 @@ struct DepBox {
     float bnd;            // the block's largest bound (infinite if one is not finite)
     int slabs, axis, per; // slabs of `per` cells along `axis`
 };
-constexpr int kDepSlabs = 8;
+constexpr int kDepSlabs = 8;        // at most
 
 // Slab t of the box (the box itself if there is one): its own box, and whether it is
 // the slab of the cell U.
@@ -222,11 +224,12 @@ __device__ __forceinline__ bool deposit_slab(const DepBox &bx, int t, int below,
 // The box of the block's live particles: I their cells, `bound` >= 0 a bound on
 // each one's contributions; nodes reach from `below` under the smallest cell to
 // `above` over the largest.  U receives the particle's unwrapped cell.  False
-// when no particle is live.  Call with the whole block (thread 0 active).
-template <int DIM>
+// when no particle is live, or without a box.  Call with the whole block (thread 0
+// active).
+template <int DIM, bool WINDOW>
 __device__ __forceinline__ bool deposit_box(DepShared &sh, const int I[3], bool live, float bound,
-                                            const PicGrid &G, int below, int above, int cap, int U[3],
-                                            DepBox &bx) {
+                                            const PicGrid &G, int below, int above, int cap,
+                                            int max_slabs, int U[3], DepBox &bx) {
     if (threadIdx.x == 0) {
         for (int a = 0; a < 3; ++a) {
             sh.ref[a] = I[a];
@@ -276,13 +279,16 @@ __device__ __forceinline__ bool deposit_box(DepShared &sh, const int I[3], bool 
     int64_t vol = (int64_t)bx.ext[0] * bx.ext[1] * bx.ext[2];
     if (vol <= cap) return true;
     {
-        int wide = 0, len = bx.ext[0];
+        int wide = 0, len = bx.ext[0], area = 1;      // the widest axis, and the section across it
 #pragma unroll
         for (int b = 1; b < DIM; ++b)
             if (bx.ext[b] > len) { wide = b; len = bx.ext[b]; }
-        const int per = (int)min<int64_t>(cap / (vol / len), 0x3fffffff) - below - above;
+#pragma unroll
+        for (int b = 0; b < DIM; ++b)
+            if (b != wide) area = min(area * min(bx.ext[b], cap + 1), cap + 1);
+        const int per = cap / area - below - above;
         const int n_cells = len - below - above;
-        if (per >= 1 && n_cells <= kDepSlabs * per) {
+        if (per >= 1 && n_cells <= max_slabs * per) {
             bx.axis = wide;
             bx.slabs = (n_cells + per - 1) / per;
             bx.per = (n_cells + bx.slabs - 1) / bx.slabs;   // even slabs,
@@ -290,6 +296,7 @@ __device__ __forceinline__ bool deposit_box(DepShared &sh, const int I[3], bool 
             return true;
         }
     }
+    if (!WINDOW) return false;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
         const float v = wave_sum_f(live ? (float)(U[a] - sh.ref[a]) : 0.0f);
@@ -352,11 +359,11 @@ __device__ __forceinline__ uint32_t box_node(int l, const uint32_t *row, const D
 // that could lose bits a float would keep, and one whose weight or position is
 // not finite, adds to the grid directly.  At most 2^8 contributions of at most
 // 2^44 units meet on a node, so a sum stays below 2^53 and its conversion back
-// is exact too: a node's block sum is rounded once.  A block most of whose
-// particles lie outside the window (an unsorted ensemble) goes direct.
+// is exact too: a node's block sum is rounded once.  A block without a box (an
+// unsorted ensemble) goes direct.
 //
-// The sort and the deposit of 4.0 M electrons at 1/4 per cell on 256^3 take 263 us
-// where the direct adds took 896.  At that density a block's box is 6 nodes a particle
+// The sort and the deposit of 4.0 M electrons at 1/4 per cell on 256^3 take 264 us
+// where the direct adds took 900.  At that density a block's box is 6 nodes a particle
 // whatever its size, so small blocks win as long as a block that straddles two tile
 // rows keeps to one or two slabs: 292 us with 128 particles and 2048 nodes, 333 with 512
 // and 6144, 497 with 1024 and 7936.  With 256 the blocks in flight decide: five a
@@ -373,9 +380,62 @@ __device__ __forceinline__ unsigned long long fixed64(float v, double scale) {
     return (unsigned long long)(__double_as_longlong(b) - 0x4338000000000000ll);
 }
 
+// A particle's charge on its nodes, as add(offsets a, b, c in 0..1 from its cell, value).
+template <int DIM, typename ADD>
+__device__ __forceinline__ void charge_each(const float F[3], float qw, ADD &&add) {
+#pragma unroll
+    for (int c = 0; c < (DIM == 3 ? 2 : 1); ++c)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int a = 0; a < 2; ++a) {
+                const float wt = (a ? F[0] : 1.0f - F[0]) * (b ? F[1] : 1.0f - F[1]) *
+                                 (DIM == 3 ? (c ? F[2] : 1.0f - F[2]) : 1.0f);
+                add(a, b, c, qw * wt);
+            }
+}
+template <int DIM>
+__device__ __forceinline__ void charge_direct(const int I[3], const float F[3], float qw, const PicGrid &G,
+                                              float *__restrict__ rho) {
+    charge_each<DIM>(F, qw, [&](int a, int b, int c, float v) {
+        const int i = node(I[0], 1 + a, G.n[0]), j = node(I[1], 1 + b, G.n[1]);
+        const int k = DIM == 3 ? node(I[2], 1 + c, G.n[2]) : 0;
+        unsafeAtomicAdd(&rho[cell(i, j, k, G)], v);
+    });
+}
+
+// The direct adds alone, for what the box does not pay for: a box block is a chain of
+// some 3 us and 2 us a slab, and where few particles share a node it adds as often.
+// Box against direct, us, sorted and one cell of drift later (3D / 2D, electrons, per
+// cell): 12 000 at 2: 6.5 against 6.4; 80 000 at 1/2: 9 and 13 against 19 and 25 in 3D, 7.6
+// and 8.3 against 9.2 and 10.1 in 2D; 80 000 at 0.03: 24 and 35 against 28 and 31, and 22 and
+// 24 against 15 and 16; 20 000 at 0.06: 17 and 24 against 8 and 9, and 11 and 13 against 6.
+// From 2^21 adds on a box is sought at any density (a set can be dense in a thin part of
+// its grid): 300 000 unsorted 120 against 118 us, sorted at 0.03 56 against 98.  Eight
+// slabs at that size: 1 M at 0.06 in 2D 68 us, 91 with up to two; below it four: 80 000 at
+// 1/2 three cells of drift after the sort 34 us, 43 with up to eight.
+constexpr int64_t kRhoAnyAdds = (int64_t)1 << 21, kRhoMinAdds = 196608;
+constexpr double kRhoMinPairs = 16384.0;      // n^2 / cells
+inline int rho_slabs(int64_t n, int dim, double cells) {      // 0: direct
+    const int64_t adds = n << dim;
+    if (adds >= kRhoAnyAdds) return kDepSlabs;
+    return adds >= kRhoMinAdds && (double)n * (double)n >= kRhoMinPairs * cells ? 4 : 0;
+}
+template <int DIM>
+__global__ __launch_bounds__(kRhoThreads) void rho_direct_kernel(sr_particles_f32 P, PicGrid G, float qv,
+                                                                 float *__restrict__ rho) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p >= P.n) return;
+    const uint32_t u = (uint32_t)p;
+    int I[3] = {0, 0, 0};
+    float F[3] = {0.0f, 0.0f, 0.0f};
+    for (int a = 0; a < DIM; ++a) locate(ld(P.x[a], u), G.inv_hi[a], G.inv_lo[a], G.n[a], I[a], F[a]);
+    charge_direct<DIM>(I, F, qv * ld(P.w, u) / G.dV, G, rho);
+}
+
 template <int DIM>
 __global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))) void rho_kernel(sr_particles_f32 P, PicGrid G, float qv,
-                                                          float *__restrict__ rho) {
+                                                          float *__restrict__ rho, int max_slabs) {
     __shared__ unsigned long long box[kRhoCells];
     __shared__ uint32_t row[kRhoCells / 2];      // a box is at least 2 nodes wide
     __shared__ DepShared sh;
@@ -386,45 +446,23 @@ __global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))
     float F[3] = {0.0f, 0.0f, 0.0f};
     for (int a = 0; a < DIM; ++a) locate(ld(P.x[a], u), G.inv_hi[a], G.inv_lo[a], G.n[a], I[a], F[a]);
     const float qw = qv * ld(P.w, u) / G.dV;
-    const auto each = [&](auto &&add) {
-#pragma unroll
-        for (int c = 0; c < (DIM == 3 ? 2 : 1); ++c)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int a = 0; a < 2; ++a) {
-                    const float wt = (a ? F[0] : 1.0f - F[0]) * (b ? F[1] : 1.0f - F[1]) *
-                                     (DIM == 3 ? (c ? F[2] : 1.0f - F[2]) : 1.0f);
-                    add(a, b, c, qw * wt);
-                }
-    };
     bool fin = fabsf(qw) <= 3.0e38f;
     for (int a = 0; a < DIM; ++a) fin = fin && fabsf(F[a]) <= 1.0f;
     const bool live = active && fin && qw != 0.0f;
     int U[3];
     DepBox bx;
-    const bool any = deposit_box<DIM>(sh, I, live, fabsf(qw), G, 0, 1, kRhoCells, U, bx);
-    bool in_win = live && any && fabsf(qw) * 262144.0f >= bx.bnd;
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        const int b = U[a] - bx.org[a];
-        in_win = in_win && b >= 0 && b + 1 <= bx.ext[a] - 1;
-    }
-    const bool use_box = 2 * __syncthreads_count(in_win) >= __syncthreads_count(live) && any;
-    in_win = in_win && use_box;
-    if (active && !in_win && (qw != 0.0f || !fin))
-        each([&](int a, int b, int c, float v) {
-            const int i = node(I[0], 1 + a, G.n[0]), j = node(I[1], 1 + b, G.n[1]);
-            const int k = DIM == 3 ? node(I[2], 1 + c, G.n[2]) : 0;
-            unsafeAtomicAdd(&rho[cell(i, j, k, G)], v);
-        });
-    if (!use_box) return;          // the condition is block-wide
+    const bool boxed =
+        deposit_box<DIM, false>(sh, I, live, fabsf(qw), G, 0, 1, kRhoCells, max_slabs, U, bx);
+    const bool in_box = live && boxed && fabsf(qw) * 262144.0f >= bx.bnd;
+    if (active && !in_box && (qw != 0.0f || !fin))
+        charge_direct<DIM>(I, F, qw, G, rho);
+    if (!boxed) return;            // the condition is block-wide
     int e = 0;
     (void)frexpf(bx.bnd, &e);      // bnd < 2^e
     const double to_fix = ldexp(1.0, kRhoBits - e), from_fix = ldexp(1.0, e - kRhoBits);
     for (int t = 0; t < bx.slabs; ++t) {
         DepBox w;
-        const bool mine = deposit_slab<DIM>(bx, t, 0, 1, U, w) && in_win;
+        const bool mine = deposit_slab<DIM>(bx, t, 0, 1, U, w) && in_box;
         const int cells = w.ext[0] * w.ext[1] * w.ext[2];
         if (t) __syncthreads();        // the box is flushed
         for (int q = threadIdx.x; q < cells; q += kRhoThreads) box[q] = 0;
@@ -433,7 +471,7 @@ __global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))
         if (mine) {
             const int l0 = (U[0] - w.org[0]) +
                            w.ext[0] * ((U[1] - w.org[1]) + w.ext[1] * (DIM == 3 ? U[2] - w.org[2] : 0));
-            each([&](int a, int b, int c, float v) {
+            charge_each<DIM>(F, qw, [&](int a, int b, int c, float v) {
                 atomicAdd(&box[l0 + a + w.ext[0] * (b + w.ext[1] * c)], fixed64(v, to_fix));
             });
         }
@@ -707,7 +745,7 @@ __global__ __launch_bounds__(kDepThreads) __attribute__((amdgpu_waves_per_eu(6))
     // ceil(n / kDepThreads) blocks
     int U[3];
     DepBox bx;
-    if (!deposit_box<DIM>(sh, m.I, m.live, m.bound, G, 1, 2, kDepCells, U, bx))
+    if (!deposit_box<DIM, true>(sh, m.I, m.live, m.bound, G, 1, 2, kDepCells, kDepSlabs, U, bx))
         return;                     // no live particle (the condition is block-wide)
     const float bnd = bx.bnd;
     if (!(bnd > 0.0f)) return;      // block-wide: every contribution is zero
@@ -884,8 +922,15 @@ extern "C" int sr_deposit_rho(const sr_particles_f32 *parts, const sr_grid *grid
         return SR_E_INVAL;
     const unsigned nb = (unsigned)((parts->n + kRhoThreads - 1) / kRhoThreads);
     hipStream_t st = (hipStream_t)stream;
-    if (grid->dim == 3) rho_kernel<3><<<nb, kRhoThreads, 0, st>>>(*parts, G, (float)charge, rho);
-    else rho_kernel<2><<<nb, kRhoThreads, 0, st>>>(*parts, G, (float)charge, rho);
+    const int slabs = rho_slabs(parts->n, grid->dim, (double)G.n[0] * G.n[1] * G.n[2]);
+    const float qv = (float)charge;
+    if (grid->dim == 3) {
+        if (slabs) rho_kernel<3><<<nb, kRhoThreads, 0, st>>>(*parts, G, qv, rho, slabs);
+        else rho_direct_kernel<3><<<nb, kRhoThreads, 0, st>>>(*parts, G, qv, rho);
+    } else {
+        if (slabs) rho_kernel<2><<<nb, kRhoThreads, 0, st>>>(*parts, G, qv, rho, slabs);
+        else rho_direct_kernel<2><<<nb, kRhoThreads, 0, st>>>(*parts, G, qv, rho);
+    }
     SR_HIP_CHECK(hipGetLastError());
     return SR_OK;
 }
