@@ -1,6 +1,6 @@
-"""The deposits' ways by size, against the 64-bit oracle: the charge added directly, in a
-box and in slabs; the current in slabs, and the accuracy of light particles beside a heavy
-one there."""
+"""The deposits on both sides of the sizes at which they change their way, against the
+64-bit oracle: the charge added directly, in a box and in slabs; the current in up to two
+slabs and up to eight, and the accuracy of light particles beside a heavy one there."""
 from __future__ import annotations
 
 import numpy as np
@@ -51,6 +51,8 @@ def test_charge_on_both_sides_of_the_rule(sr, dim, n, count, weights, order):
 
 
 @pytest.mark.parametrize("dim, n, count, drift, heavy", [
+    (3, (256, 64, 4), 196607, 60.0, 1.0),       # two slabs at most: windows
+    (3, (256, 64, 4), 196609, 60.0, 1.0),       # up to eight
     (3, (256, 64, 4), 200000, 60.0, 1e6),       # one heavy particle a block, and light ones
     (2, (2000, 64, 1), 200000, 300.0, 1e6),
 ])
