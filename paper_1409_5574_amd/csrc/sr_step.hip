@@ -1319,8 +1319,25 @@ __global__ __launch_bounds__(kBlock) void epilogue_second_kernel(
 // 0.46 ms; as one wave per chunk 1.33 ms (0.73 ms with the waves split but wave 0
 // not yet stripped of what only a photon needs; batches of 4, 8, 16 steps 0.467,
 // 0.456, 0.459 ms; without the ledger wave 0.444 ms, so wave 0 is the chain).
+//
+// Four blocks fit a compute unit, 1024 chunks the chip.  With more, what counts is the
+// work, and a chunk to a wave has less of it (push_emit_steps_wave_kernel).  100 steps,
+// us, four waves a chunk against one:
+//   chunks            1024        1536        2048        4096        8192
+//   S, K = 1        81 / 154   127 / 180   148 / 181   257 / 271   476 / 474
+//   S, K = 8       198 / 407   251 / 455   333 / 457   571 / 624  1067 / 1080
+//   S, K = 16      317 / 697   517 / 766   616 / 767  1159 / 1041 2220 / 1802
+//   table, K = 1    73 / 135   125 / 163   144 / 164   261 / 245   482 / 425
+//   table, K = 8   154 / 284   262 / 313   287 / 315   516 / 417   932 / 712
+//   quantum, K = 2 122 / 209   213 / 242   245 / 242   427 / 361   781 / 629
+//   quantum, K = 8 325 / 490   582 / 553   634 / 554  1168 / 796  2132 / 1402
 template <int KMAX>
-constexpr int kStepsBatch = KMAX >= 8 ? 1 : 8 / KMAX;   // T: 33 KB of LDS, four blocks per CU
+constexpr int kStepsBatch = KMAX >= 8 ? 1 : 8 / KMAX;   // T
+// The most chunks that four waves each take faster.
+template <int KMAX, int SAMPLER>
+constexpr int64_t kStepsSplitChunks = SAMPLER == SR_SAMPLER_S       ? (KMAX <= 8 ? 4096 : 2048)
+                                      : SAMPLER == SR_SAMPLER_TABLE ? 2048
+                                                                    : (KMAX <= 4 ? 1536 : 1024);
 
 template <int KMAX>
 struct StepsSmem {
@@ -1360,6 +1377,7 @@ __global__ __launch_bounds__(kBlock) void push_emit_steps_kernel(const StepArgs<
                                                                  int64_t n_steps) {
     constexpr int T = kStepsBatch<KMAX>;
     __shared__ StepsSmem<KMAX> sm;
+    static_assert(sizeof(StepsSmem<KMAX>) <= 160 * 1024 / 4, "four blocks per compute unit");
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t c = blockIdx.x;                      // chunk = block
@@ -1456,7 +1474,8 @@ __global__ __launch_bounds__(kBlock) void push_emit_steps_kernel(const StepArgs<
     uint32_t run_base = 0;
     float g_old = gamma_of<float>(p);
     __syncthreads();
-    // Lanes past the chunk's end run along at p = 0 with rate 0 and weight 0.
+    // Lanes past the chunk's end are pushed along from rest with rate 0, chi 0 and weight 0,
+    // and reset like any other where the push is not finite.
     // What a step without photons does not need is kept out of its way: it
     // branches only on wave-uniform conditions.
     for (int64_t b = 1; b < batches + 2; ++b) {
@@ -1605,6 +1624,188 @@ __global__ __launch_bounds__(kBlock) void push_emit_steps_kernel(const StepArgs<
         }
     }
     if (lane == 0) cold_args<float>().seg_count[c] = run_base;
+}
+
+// The same with one wave per chunk, which does a step's parts one after another: more
+// of its chunks fit a compute unit and nothing passes through LDS, so it is the faster one
+// once the chip is full.
+template <int KMAX, int SAMPLER>
+__global__ __launch_bounds__(64) void push_emit_steps_wave_kernel(const StepArgs<float> a,
+                                                                  int64_t n_steps) {
+    const int lane = threadIdx.x;
+    const uint32_t c = blockIdx.x;                      // chunk = wave = block
+    const uint32_t s0 = c * (uint32_t)kChunk;
+    const uint32_t e0 = min(s0 + (uint32_t)kChunk, (uint32_t)a.n);
+    const uint32_t i = s0 + lane;
+    const bool active = i < e0;
+    const uint32_t pp = (uint32_t)a.per_particle;
+    const uint32_t seg_base = s0 * pp, seg_cap = (e0 - s0) * pp;
+    const PhotonOut P = cold_args<float>();
+    const int K = a.K;
+    const float invK = 1.0f / (float)K;
+    const int64_t nb = gridDim.x;
+
+    float wi = 0.0f, pos[3] = {0.0f, 0.0f, 0.0f}, p[3] = {0.0f, 0.0f, 0.0f};
+    uint32_t pid = 0;
+    if (active) {
+        wi = ld(a.w, i);
+        pid = ld(a.id, i);
+        if (a.has_pos) {
+            pos[0] = ld(a.x[0], i);
+            if (a.x[1]) pos[1] = ld(a.x[1], i);
+            if (a.x[2]) pos[2] = ld(a.x[2], i);
+        }
+        p[0] = ld(a.p[0], i); p[1] = ld(a.p[1], i); p[2] = ld(a.p[2], i);
+    }
+    const float E[3] = {a.g.e0[0], a.g.e0[1], a.g.e0[2]};
+    const float B[3] = {a.g.b0[0], a.g.b0[1], a.g.b0[2]};
+    uint32_t run_base = 0;
+    for (int64_t si = 0; si < n_steps; ++si) {
+        const uint32_t step = a.step + (uint32_t)si;
+        double acc_emit = 0.0, acc_ll = 0.0, acc_de = 0.0, acc_clamp = 0.0, acc_drop = 0.0;
+        float chif = 0.0f, eps_unit = 0.0f, Hf = 0.0f, dirf[3] = {0.0f, 0.0f, 0.0f};
+        float pn[3] = {p[0], p[1], p[2]}, gb = 1.0f, g_new = 1.0f, p2 = 0.0f, pbm = 0.0f,
+              chi = 0.0f;
+        uint32_t flags = 0;
+        bool bad = false;
+        if (active) {
+            const Pushed<float> q = push_fields<float>(a, p, E, B);
+            pn[0] = q.pn[0]; pn[1] = q.pn[1]; pn[2] = q.pn[2];
+            p2 = q.p2; gb = q.gb; g_new = q.g_new; pbm = q.pbm; chi = q.chi;
+            Hf = q.H;
+            chif = q.chi;
+            bad = q.bad;
+            if (bad) flags |= SR_W_NONFINITE;
+            if (pbm > 0.0f) {
+                const float inv = rcp_r<float>(pbm);
+                dirf[0] = q.pb[0] * inv; dirf[1] = q.pb[1] * inv; dirf[2] = q.pb[2] * inv;
+            }
+            eps_unit = 1.5f * chif * gb;
+        }
+        float delta_ph = 0.0f;
+        uint32_t wave_tot = 0;
+        float2 rr = make_float2(1.0f, 0.0f);
+        if (SAMPLER == SR_SAMPLER_TABLE && active && a.kin_cut) rr = r_lookup(a.tab.r, chif);
+        constexpr bool kProposal = SAMPLER == SR_SAMPLER_S || SAMPLER == SR_SAMPLER_QUANTUM;
+        const float rate = !active ? 0.0f : (kProposal ? a.rate_c * Hf : a.direct_c * Hf * rr.x);
+        const TrialCut cut = trial_cut(SAMPLER == SR_SAMPLER_S && a.kin_cut != 0, chif);
+        uint4 words = make_uint4(0, 0, 0, 0);
+        for (int k = 0; k < KMAX; ++k) {
+            if (k >= K) break;
+            if ((k & 1) == 0)
+                words = philox4x32_10(make_uint4(pid, step, (uint32_t)(k >> 1), 0u), a.seed_lo,
+                                      a.seed_hi);
+            const uint32_t wa = (k & 1) ? words.z : words.x;
+            const uint32_t wb = (k & 1) ? words.w : words.y;
+            float dn = rate, lg = 0.0f, xq = 0.0f;
+            bool lower = true;
+            if (SAMPLER == SR_SAMPLER_S) {
+                dn = rate * trial_q(wa, a.tab.gtab, a.tab.pa, lg, lower);
+                if (trial_is_cut(cut, lg, lower)) dn = 0.0f;
+            } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
+                dn = rate * quantum_q(wa, a.tab.qtab, a.tab.pa, chif, xq);
+            }
+            bool emit;
+            float frac = invK;
+            if (dn >= 1.0f) {
+                emit = true;
+                if (a.dn_policy == SR_DN_WEIGHT) frac = dn * invK;
+            } else {
+                emit = wb < (uint32_t)(dn * 4294967296.0f);
+            }
+            const uint64_t m = __ballot(emit);
+            if (m) {
+                if (emit) {
+                    float x;
+                    if (SAMPLER == SR_SAMPLER_S) {
+                        x = trial_x(wa, lg, lower);
+                    } else if (SAMPLER == SR_SAMPLER_QUANTUM) {
+                        x = xq;
+                    } else {
+                        float lnU, ln1mU;
+                        direct_u(wa, rr, lnU, ln1mU);
+                        x = __builtin_amdgcn_exp2f(t1_log2x(a.tab.t1, lnU, ln1mU));
+                    }
+                    const float eps = eps_unit * x;
+                    const float wph = wi * frac;
+                    delta_ph += frac * eps;
+                    const uint32_t slot = run_base + wave_tot + lane_prefix(m);
+                    if (slot < seg_cap) {
+                        store_photon(P, seg_base + slot, eps, wph, dirf, pos, pid, (uint32_t)k, step);
+                    } else {
+                        acc_drop += (double)wph * (double)eps;
+                        flags |= SR_W_PHOTON_OVERFLOW;
+                    }
+                }
+                wave_tot += (uint32_t)__popcll(m);
+            }
+        }
+        float acc_w = 0.0f;
+        if (active) {
+            acc_emit = (double)wi * (double)delta_ph;
+            const float beta2 = p2 * rcp_r<float>(gb * gb);
+            if (!bad) acc_ll = (double)(wi * a.ll_c * chi * chi * beta2);
+            float delta = 0.0f;
+            if (a.recoil == SR_RECOIL_PHOTON) delta = delta_ph;
+            else if (a.recoil == SR_RECOIL_LL) delta = a.ll_c * chi * chi * pbm * rcp_r<float>(gb);
+            float g_after = g_new;
+            if (delta > 0.0f) {
+                const float pm = sqrt_r<float>(pn[0] * pn[0] + pn[1] * pn[1] + pn[2] * pn[2]);
+                float fac = pm > 0.0f ? 1.0f - delta * rcp_r<float>(pm) : -1.0f;
+                float removed = delta;
+                if (fac < 0.0f) {
+                    acc_clamp = (double)(wi * (delta - pm));
+                    removed = pm;
+                    fac = 0.0f;
+                    flags |= SR_W_RECOIL_CLAMP;
+                }
+                pn[0] *= fac; pn[1] *= fac; pn[2] *= fac;
+                const float pm_after = fac * pm;
+                g_after = sqrt_r<float>(1.0f + pm_after * pm_after);
+                acc_de = (double)(-wi * removed * (pm_after + pm) * rcp_r<float>(g_after + g_new));
+            }
+            if (a.push_position && a.has_pos) {
+                const float vdt = a.dt * rcp_r<float>(g_after);
+                pos[0] += vdt * pn[0]; pos[1] += vdt * pn[1]; pos[2] += vdt * pn[2];
+            }
+            p[0] = pn[0]; p[1] = pn[1]; p[2] = pn[2];
+            acc_w = wi;
+        }
+        run_base += wave_tot;
+        // this wave's partial ledger row of the step (fixed-order wave sums)
+        const double se = wave_sum(acc_emit), sl = wave_sum(acc_ll), sd = wave_sum(acc_de);
+        const double sc = __ballot(acc_clamp != 0.0) ? wave_sum(acc_clamp) : 0.0;
+        const double sdr = __ballot(acc_drop != 0.0) ? wave_sum(acc_drop) : 0.0;
+        const float sw = wave_sum_f(acc_w), cm = wave_max(chif);
+        uint32_t wf = 0;
+        if (__ballot(flags != 0)) {
+            wf = flags;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) wf |= (uint32_t)__shfl_xor((int)wf, o, 64);
+        }
+        if (lane == 0) {
+            double *row = P.partials + (si * nb + c) * kPartCols;
+            row[SR_LED_EMITTED] = se;
+            row[SR_LED_LL] = sl;
+            row[SR_LED_RECOIL] = sd;
+            row[SR_LED_CLAMPED] = sc;
+            row[SR_LED_DROPPED] = sdr;
+            row[SR_LED_PHOTONS] = (double)wave_tot;
+            row[SR_LED_WEIGHT] = (double)sw;
+            row[SR_LED_CHI_MAX] = (double)cm;
+            row[kPartFlags] = (double)wf;
+            row[kPartFlags + 1] = 0.0;
+        }
+    }
+    if (active) {
+        st(a.p[0], i, p[0]); st(a.p[1], i, p[1]); st(a.p[2], i, p[2]);
+        if (a.push_position && a.has_pos) {
+            st(a.x[0], i, pos[0]);
+            if (a.x[1]) st(a.x[1], i, pos[1]);
+            if (a.x[2]) st(a.x[2], i, pos[2]);
+        }
+    }
+    if (lane == 0) P.seg_count[c] = run_base;
 }
 
 // Ledger row s of a multi-step launch: the nb partial rows of step s, summed in
@@ -1847,7 +2048,11 @@ int launch_steps(sr_particles_f32 *parts, const sr_grid *grid, double dt, uint64
     const int K = prm->n_samples;
     const int KM = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : K <= 8 ? 8 : 16;
     const unsigned nb = (unsigned)n_chunks;
-#define SR_STEPS(KMV, SMP) push_emit_steps_kernel<KMV, SMP><<<nb, kBlock, 0, st>>>(a, n_steps)
+#define SR_STEPS(KMV, SMP)                                                              \
+    if (n_chunks <= kStepsSplitChunks<KMV, SMP>)                                        \
+        push_emit_steps_kernel<KMV, SMP><<<nb, kBlock, 0, st>>>(a, n_steps);            \
+    else                                                                                \
+        push_emit_steps_wave_kernel<KMV, SMP><<<nb, 64, 0, st>>>(a, n_steps)
 #define SR_STEPS_K(SMP)                      \
     switch (KM) {                            \
         case 1: SR_STEPS(1, SMP); break;     \
