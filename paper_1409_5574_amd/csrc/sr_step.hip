@@ -1418,6 +1418,7 @@ __global__ __launch_bounds__(kBlock) void push_emit_steps_kernel(const StepArgs<
     if (wave == 1) {
         // ---- partial ledger rows of batch b - 2 (fixed-order wave sums)
         const float sw = wave_sum_f(wi);
+        const bool odd = !isfinite(wi);      // its product with no photon is not zero
         double *const partials = cold_args<float>().partials;
         for (int64_t b = 0; b < batches + 2; ++b) {
             if (b >= 2) {
@@ -1430,7 +1431,7 @@ __global__ __launch_bounds__(kBlock) void push_emit_steps_kernel(const StepArgs<
                     const float gb = sm.gb[h][t][lane];
                     // Landau-Lifshitz loss of the step (eq:LLformOfRRForce)
                     const float beta2 = v.w * rcp_r<float>(gb * gb);
-                    const double se = __ballot(v.x != 0.0f) ? wave_sum((double)wi * (double)v.x) : 0.0;
+                    const double se = __ballot(v.x != 0.0f || odd) ? wave_sum((double)wi * (double)v.x) : 0.0;
                     const double sl = wave_sum((double)(wi * a.ll_c * v.z * v.z * beta2));
                     const double sd = __ballot(v.y != 0.0f) ? wave_sum((double)v.y) : 0.0;
                     const float cm = wave_max(v.z);

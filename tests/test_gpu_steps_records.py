@@ -1,6 +1,6 @@
 """The multi-step launch's photon records and its two kernels: every field of every record
-against single-step launches, segments that fill up in mid-launch, and launches with more
-chunks than four waves each are given."""
+against single-step launches, segments that fill up in mid-launch, launches with more chunks
+than four waves each are given, and a weight that is not finite."""
 from __future__ import annotations
 
 import numpy as np
@@ -122,3 +122,22 @@ def test_one_wave_a_chunk_equals_four(sr, table, chunks, K, sampler):
     # 64-bit sums (the weights' of 32-bit ones, exact here) in another order
     np.testing.assert_allclose(r[:, :7], parts[0][1][:, :7] + parts[1][1][:, :7], rtol=1e-11)
     assert np.array_equal(r[:, 7], np.maximum(parts[0][1][:, 7], parts[1][1][:, 7]))
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_nonfinite_weight_shows_in_every_row(sr, table, bad):
+    """A weight that is not finite makes the energy sums of every step that, as one step a
+    call does, whether or not the particle emits."""
+    cfg = synth.config("c1")
+    n, steps = 70, 6
+    st = synth.gen_particles(cfg, n=n, seed=2)
+    st["w"][5] = bad
+    prm = sr.params_struct(cfg.hbar_n, cfg.alpha, 1)
+    print(f"[gpu-case] steps weight {bad}", flush=True)
+    _, rows, _ = _launches(sr, table, st, [steps], prm, 64)
+    parts, grid = sr.Particles.from_numpy(st, dim=0), sr.grid_struct(0, e0=(0.1, 0.0, 0.2), b0=(0.3, 0.0, 40.0))
+    ph, ledger = sr.PhotonBuffer(n, 64, dim=3), sr.LedgerBuf(1, sr.n_chunks_uniform(n))
+    for s in range(steps):
+        sr.gather_push_emit(parts, None, grid, cfg.dt, 0xBA7C4, 3 + s, prm, table, ph, ledger, 0)
+        one = ledger.row(0)
+        assert np.array_equal(np.isnan(one[:2]), np.isnan(rows[s, :2])), (s, one, rows[s])
