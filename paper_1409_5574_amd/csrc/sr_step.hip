@@ -470,10 +470,16 @@ constexpr int step_waves_per_eu() {
     return DIM == 3 && KMAX <= 8 ? 5 : 1;
 }
 
-// At most; the FP64 path has no sort (2^20 electrons on 192x192x96: 474 us with four waves per SIMD, 475.5
-// with the five that its 90 VGPRs allow).
+// At most.  The FP64 path has no sort, and its gather reads less of what other waves fetched
+// the more of them there are, but it needs some to fill the chip: 2D, 16 trials, 2^20
+// electrons 231 us with four waves per SIMD, 234 with five, 238 with seven, 300 000 79, 75
+// and 75 (1 trial 62, 61, 61); 3D, 8 trials, 2^20 446 with four and 448 with the five that 90 VGPRs
+// allow.  In a uniform field (no gather) the more the better: 8 trials, 2^20, 50 and 45 us.
 template <typename R, int DIM>
-constexpr int step_waves_max() { return sizeof(R) != 4 ? 4 : DIM == 3 ? 5 : 8; }
+constexpr int step_waves_max() {
+    if (sizeof(R) != 4) return DIM == 3 ? 4 : DIM == 2 ? 5 : 8;
+    return DIM == 3 ? 5 : 8;
+}
 
 // FLOOR: the grid-frequency floor is on (a.e_grid > 0); a template flag, so the
 // kernels without it carry none of its code.
