@@ -469,10 +469,18 @@ __device__ __forceinline__ XPair x_pair(uint32_t ix, int nx) {
     p.any_wrap = __ballot(p.wrap) != 0;
     return p;
 }
-template <typename R>
+// That load waits for its row's pair, row by row: 24 latencies and more in 3D for a wave
+// that wraps.  With FLAT a wave that wraps issues every row's second load with the first
+// (more registers), for the kernel in which the block's other waves wait for it.
+template <typename R, bool FLAT = false>
 __device__ __forceinline__ R row_lerp(const float *__restrict__ a, uint32_t row, const XPair &p,
                                       R gx, R fx) {
     const float2 v = ld2(a, row + p.start);
+    if constexpr (FLAT) {
+        float first = 0.0f;
+        if (p.any_wrap) first = ld(a, row);
+        return fma_r<R>(gx, (R)(p.wrap ? v.y : v.x), fx * (R)(p.wrap ? first : v.y));
+    }
     float lo = v.x, hi = v.y;
     if (p.any_wrap && p.wrap) {
         lo = v.y;
@@ -492,7 +500,7 @@ __device__ __forceinline__ R trilerp(R gy, R fy, R gz, R fz, R c00, R c01, R c10
 // Bilinear (2D) / trilinear (3D) interpolation of one component.  sx, sy, sz
 // select offset 0 (false) or 1/2 (true) on each axis; P0 / P1 are the x pairs
 // of the two offsets.
-template <typename R, int DIM>
+template <typename R, int DIM, bool FLAT = false>
 __device__ __forceinline__ R cic(const float *__restrict__ a, const Axis<R> &X, const Axis<R> &Y,
                                  const Axis<R> &Z, const XPair &P0, const XPair &P1, bool sx,
                                  bool sy, bool sz, int nx, int ny) {
@@ -503,7 +511,7 @@ __device__ __forceinline__ R cic(const float *__restrict__ a, const Axis<R> &X, 
     const R gx = (R)1 - fx, gy = (R)1 - fy;
     if (DIM == 2) {
         const uint32_t r0 = __umul24(iy0, (uint32_t)nx), r1 = __umul24(iy1, (uint32_t)nx);
-        return fma_r<R>(gy, row_lerp<R>(a, r0, P, gx, fx), fy * row_lerp<R>(a, r1, P, gx, fx));
+        return fma_r<R>(gy, row_lerp<R, FLAT>(a, r0, P, gx, fx), fy * row_lerp<R, FLAT>(a, r1, P, gx, fx));
     } else {
         const uint32_t iz0 = sz ? Z.i1 : Z.i0, iz1 = sz ? Z.i1p : Z.i0p;
         const R fz = sz ? Z.f1 : Z.f0;
@@ -513,8 +521,8 @@ __device__ __forceinline__ R cic(const float *__restrict__ a, const Axis<R> &X, 
         const uint32_t z0 = __umul24(iz0, (uint32_t)ny), z1 = __umul24(iz1, (uint32_t)ny);
         const uint32_t p00 = __umul24(z0 + iy0, (uint32_t)nx), p01 = __umul24(z0 + iy1, (uint32_t)nx);
         const uint32_t p10 = __umul24(z1 + iy0, (uint32_t)nx), p11 = __umul24(z1 + iy1, (uint32_t)nx);
-        const R c00 = row_lerp<R>(a, p00, P, gx, fx), c01 = row_lerp<R>(a, p01, P, gx, fx);
-        const R c10 = row_lerp<R>(a, p10, P, gx, fx), c11 = row_lerp<R>(a, p11, P, gx, fx);
+        const R c00 = row_lerp<R, FLAT>(a, p00, P, gx, fx), c01 = row_lerp<R, FLAT>(a, p01, P, gx, fx);
+        const R c10 = row_lerp<R, FLAT>(a, p10, P, gx, fx), c11 = row_lerp<R, FLAT>(a, p11, P, gx, fx);
         return trilerp<R>(gy, fy, gz, fz, c00, c01, c10, c11);
     }
 }

@@ -77,7 +77,7 @@ __device__ __forceinline__ void setup_axis<double>(const GridK &g, int ax, doubl
     axis_setup(x, g.inv_d[ax], g.n[ax], A);
 }
 
-template <typename R, int DIM>
+template <typename R, int DIM, bool FLAT = false>
 __device__ __forceinline__ void gather_grid(const StepArgs<R> &a, const R pos[3], R E[3], R B[3]) {
     Axis<R> X, Y, Z;
     setup_axis<R>(a.g, 0, pos[0], X);
@@ -87,12 +87,12 @@ __device__ __forceinline__ void gather_grid(const StepArgs<R> &a, const R pos[3]
     const int nx = a.g.n[0], ny = a.g.n[1];
     const XPair P0 = x_pair(X.i0, nx), P1 = x_pair(X.i1, nx);
     // Yee offsets: Ex(1/2,0,0) Ey(0,1/2,0) Ez(0,0,1/2) Bx(0,1/2,1/2) By(1/2,0,1/2) Bz(1/2,1/2,0)
-    E[0] = cic<R, DIM>(a.f[0], X, Y, Z, P0, P1, true, false, false, nx, ny);
-    E[1] = cic<R, DIM>(a.f[1], X, Y, Z, P0, P1, false, true, false, nx, ny);
-    E[2] = cic<R, DIM>(a.f[2], X, Y, Z, P0, P1, false, false, true, nx, ny);
-    B[0] = cic<R, DIM>(a.f[3], X, Y, Z, P0, P1, false, true, true, nx, ny);
-    B[1] = cic<R, DIM>(a.f[4], X, Y, Z, P0, P1, true, false, true, nx, ny);
-    B[2] = cic<R, DIM>(a.f[5], X, Y, Z, P0, P1, true, true, false, nx, ny);
+    E[0] = cic<R, DIM, FLAT>(a.f[0], X, Y, Z, P0, P1, true, false, false, nx, ny);
+    E[1] = cic<R, DIM, FLAT>(a.f[1], X, Y, Z, P0, P1, false, true, false, nx, ny);
+    E[2] = cic<R, DIM, FLAT>(a.f[2], X, Y, Z, P0, P1, false, false, true, nx, ny);
+    B[0] = cic<R, DIM, FLAT>(a.f[3], X, Y, Z, P0, P1, false, true, true, nx, ny);
+    B[1] = cic<R, DIM, FLAT>(a.f[4], X, Y, Z, P0, P1, true, false, true, nx, ny);
+    B[2] = cic<R, DIM, FLAT>(a.f[5], X, Y, Z, P0, P1, true, true, false, nx, ny);
 }
 
 template <typename R> __device__ __forceinline__ R box_len(const GridK &g, int q);
@@ -125,14 +125,14 @@ template <typename R>
 __device__ __forceinline__ Pushed<R> push_fields(const StepArgs<R> &a, const R p0[3], const R E[3],
                                                  const R B[3]);
 
-template <typename R, int DIM>
+template <typename R, int DIM, bool FLAT = false>
 __device__ __forceinline__ Pushed<R> push_heff(const StepArgs<R> &a, const R pos[3],
                                                const R p0[3]) {
     R E[3], B[3];
     if (DIM == 0) {
         for (int q = 0; q < 3; ++q) { E[q] = uniform_e<R>(a.g, q); B[q] = uniform_b<R>(a.g, q); }
     } else {
-        gather_grid<R, DIM>(a, pos, E, B);
+        gather_grid<R, DIM, FLAT>(a, pos, E, B);
     }
     return push_fields<R>(a, p0, E, B);
 }
@@ -288,11 +288,25 @@ enum StepMode { kUniform = 0, kBox = 1, kRagged = 2, kLoop = 3 };
 
 // Most explicit chunks for which their rounds are dealt.  That shortens the longest
 // chunks' chains, which is what a launch takes that the chip holds at once; it costs waves
-// in flight (111 registers and up, a list entry a trial), which is what a larger one needs.
-// Random cuts, 60 particles a chunk on average, quantum sampler, one wave a chunk -> dealt:
-// 5000 chunks 89 -> 76 us (4 trials), 124 -> 105 (8), 195 -> 174 (16); 8000 chunks 102 ->
-// 93 (4), 224 -> 224 (16); S sampler, 33 000 chunks 201 -> 211 (2), 488 -> 598 (16).
-constexpr int64_t kDealtChunks = 8192;
+// in flight (registers, and LDS for a list entry a trial), which is what a larger one
+// needs: with 16 trials two blocks of four chunks fit a compute unit, so chunks of few
+// rounds are dealt up to one turn of the chip only.
+// One wave a chunk against dealt, us (S sampler; random cuts of 60 and of 500 particles on
+// average, chunks of 64 and of 256 each; 2D / 3D):
+//   chunks           2000 x 60        8000 x 500       4000 x 64       1000 x 256
+//   1 trial     26, 82 / 25, 56  228,811 / 175,580  17, 45 / 16, 47  25, 56 / 23, 54
+//   8 trials   53,111 / 38, 69  517,1088 / 337,701  23, 51 / 26, 56  40, 68 / 37, 66
+//   16 trials  86,154 / 54, 82  861,1418 / 633,962  29, 58 / 37, 64  59, 86 / 52, 80
+constexpr int64_t kDealtChunks = 8192, kDealtChunks16 = 2048;
+// In 3D a launch with more than a block or so on each compute unit deals the rounds of
+// every block with several: rounds in flight side by side gather the same cache lines.
+// Even chunks of 1000, each wave its own against dealt: 1000 chunks 175 and 168 us with 1
+// trial, 199 and 222 with 8; 2000 chunks 336 and 252, 377 and 302; with 16 trials dealing
+// does not pay.
+constexpr int64_t kDealtAlways = 1536;
+inline bool deal_rounds(int64_t n, int64_t n_chunks, int K) {
+    return n_chunks <= (K <= 8 || n >= 2 * kChunk * n_chunks ? kDealtChunks : kDealtChunks16);
+}
 
 // The emitted trials of a round of explicit chunks, listed by their waves: a photon's
 // slot is known only when the block's waves have finished the round.
@@ -352,9 +366,14 @@ struct alignas(16) RoundSmem {
     };
     PhotonStage<KMAX> stage;
 };
+struct Deal {
+    uint32_t first[kWaves + 1], round0[kWaves + 1];   // of the block's chunks: bounds, first rounds
+    uint32_t run[kWaves];                             // photons so far
+};
 template <int KMAX, int HOT>
 struct alignas(16) RoundSmem<KMAX, kRagged, HOT> {
     LedgerSmem led;
+    Deal deal;
     PhotonList<64 * KMAX> list;
     float4 hot[HOT];
 };
@@ -534,24 +553,43 @@ void push_emit_kernel(const StepArgs<R> a) {
     // LDS and the block writes them together at the end (one store per array for up to
     // 256 photons of four chunks).
     constexpr bool kCanStage = SAMPLER != SR_SAMPLER_MLP && kSingle;
-    // Explicit chunks: the block's rounds, in the order of its chunks, are dealt to its
-    // waves in turn, so that a chunk of many rounds is not one wave's chain (300 007
-    // particles in 5000 chunks of 60 on average: the longest has 9 rounds).
-    uint32_t first[kWaves + 1], round0[kWaves + 1], run[kWaves];   // chunk bounds, rounds, photons
+    // Explicit chunks: a block's rounds, in the order of its chunks, are dealt to its
+    // waves in turn where one of its chunks has more than its share of them, so that a
+    // chunk of many rounds is not one wave's chain (300 007 particles in 5000 chunks of 60
+    // on average: the longest has 9 rounds).  Otherwise each wave takes its own chunk's
+    // and waits for no other.
+    uint32_t batch = 0, limit = 0;      // explicit chunks: first round of the waves' four, or the wave's
+    uint32_t own0 = 0, own1 = 0;        // rounds of the wave's own chunk
     uint32_t rounds = 0;
+    bool dealt = false;
     if constexpr (kRag) {
+        Deal &D = sm.deal;
+        uint32_t longest = 0, from = 0;
 #pragma unroll
-        for (int j = 0; j <= kWaves; ++j)
-            first[j] = (uint32_t)__builtin_amdgcn_readfirstlane(
+        for (int j = 0; j <= kWaves; ++j) {
+            const uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane(
                 (int)a.start[min((int64_t)(blk * kWaves + j), a.n_chunks)]);
-#pragma unroll
-        for (int j = 0; j < kWaves; ++j) {
-            round0[j] = rounds;
-            // (bounds that decrease hold no particle)
-            rounds += first[j + 1] > first[j] ? (first[j + 1] - first[j] + kChunk - 1) / kChunk : 0u;
-            run[j] = 0;
+            if (j > 0) {
+                // (bounds that decrease hold no particle)
+                const uint32_t m = to > from ? (to - from + kChunk - 1) / kChunk : 0u;
+                longest = max(longest, m);
+                if (j - 1 == wave) { own0 = rounds; own1 = rounds + m; }
+                rounds += m;
+            }
+            if (tid == 0) {
+                D.first[j] = to;
+                D.round0[j] = rounds;
+                if (j < kWaves) D.run[j] = 0;
+            }
+            from = to;
         }
-        round0[kWaves] = rounds;
+        own0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)own0);
+        own1 = (uint32_t)__builtin_amdgcn_readfirstlane((int)own1);
+        dealt = longest > (rounds + kWaves - 1) / kWaves ||
+                (DIM == 3 && KMAX <= 8 && a.n_chunks >= kDealtAlways && rounds > kWaves);
+        batch = dealt ? 0u : own0;
+        limit = dealt ? rounds : own1;
+        __syncthreads();
     }
     const int K = a.K;
     const float invK = 1.0f / (float)K;
@@ -574,25 +612,26 @@ void push_emit_kernel(const StepArgs<R> a) {
 
     // uniform chunks: exactly one round per wave, waves without a chunk running it with no active lane,
     // so the block-wide steps of the field box are reached by every thread
-    uint32_t batch = 0;      // explicit chunks: first round of the waves' four
-    for (uint32_t base = s0; kRag ? batch < rounds : kSingle ? base == s0 : base < e0;
-         base += kChunk, batch += kWaves) {
-        uint32_t mine = 0;   // the round's chunk in the block
+    for (uint32_t base = s0; kRag ? batch < limit : kSingle ? base == s0 : base < e0;
+         base += kChunk, batch += dealt ? (uint32_t)kWaves : 1u) {
+        uint32_t from0 = 0;  // first round of the round's chunk, and that chunk in the block
+        uint32_t mine = 0;
         if constexpr (kRag) {
-            const uint32_t r = batch + (uint32_t)__builtin_amdgcn_readfirstlane(wave);
-            const bool on = r < rounds;
-#pragma unroll
-            for (int j = 1; j < kWaves; ++j) mine += r >= round0[j] ? 1u : 0u;
+            const Deal &D = sm.deal;
+            const uint32_t r = batch + (dealt ? (uint32_t)__builtin_amdgcn_readfirstlane(wave) : 0u);
             base = 0;
             e0 = 0;
+            if (r < rounds) {
 #pragma unroll
-            for (int j = 0; j < kWaves; ++j)
-                if (on && mine == (uint32_t)j) {
-                    base = first[j] + (r - round0[j]) * kChunk;
-                    e0 = first[j + 1];
-                    seg_base = first[j] * pp;
-                    seg_cap = (e0 - first[j]) * pp;
-                }
+                for (int j = 1; j < kWaves; ++j) mine += r >= D.round0[j] ? 1u : 0u;
+                mine = (uint32_t)__builtin_amdgcn_readfirstlane((int)mine);
+                from0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)D.round0[mine]);
+                const uint32_t b0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)D.first[mine]);
+                e0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)D.first[mine + 1]);
+                base = b0 + (r - from0) * kChunk;
+                seg_base = b0 * pp;
+                seg_cap = (e0 - b0) * pp;
+            }
         }
         double acc_emit = 0.0, acc_ll = 0.0, acc_de = 0.0, acc_clamp = 0.0, acc_drop = 0.0;
         float acc_w = 0.0f;
@@ -636,7 +675,7 @@ void push_emit_kernel(const StepArgs<R> a) {
                 if (use_box) q = push_box<R>(a, pos, p0, sm.box, fb);
                 else q = push_heff<R, DIM>(a, pos, p0);
             } else {
-                q = push_heff<R, DIM>(a, pos, p0);
+                q = push_heff<R, DIM, kRag>(a, pos, p0);
             }
             pn[0] = q.pn[0]; pn[1] = q.pn[1]; pn[2] = q.pn[2];
             p2 = q.p2;
@@ -993,48 +1032,56 @@ void push_emit_kernel(const StepArgs<R> a) {
         }
         run_base += wave_tot;
         if constexpr (kRag) {
-            // the waves' counts give each its first slot; then thread (j, lane) adds what
-            // lane `lane` of chunk j's rounds has, in their order
-            LedgerSmem &rs = round_smem<BOX>(sm).led;
-            rs.d[0][tid] = acc_emit;
-            rs.d[1][tid] = acc_ll;
-            rs.d[2][tid] = acc_de;
-            rs.d[3][tid] = acc_clamp;
-            rs.f[0][tid] = acc_w;
-            if (lane == 0) rs.cnt[wave] = listed;
-            __syncthreads();
-            uint32_t slot0 = 0;
+            LedgerSmem &rs = sm.led;
+            Deal &D = sm.deal;
+            if (dealt) {
+                // the waves' counts give each its first slot; then thread (j, lane) adds what
+                // lane `lane` of chunk j's rounds has, in their order
+                rs.d[0][tid] = acc_emit;
+                rs.d[1][tid] = acc_ll;
+                rs.d[2][tid] = acc_de;
+                rs.d[3][tid] = acc_clamp;
+                rs.f[0][tid] = acc_w;
+                if (lane == 0) rs.cnt[wave] = listed;
+                __syncthreads();
+                uint32_t slot0 = D.run[mine];
 #pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t r = batch + w, n = rs.cnt[w];
+                for (int w = 0; w < kWaves - 1; ++w)
+                    if (w < wave && batch + w >= from0) slot0 += rs.cnt[w];
+                slot0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)slot0);
+                list_store(slot0);
+                list_dropped(slot0);
+                rs.d[4][tid] = acc_drop;
+                __syncthreads();
+                uint32_t more = 0;
 #pragma unroll
-                for (int j = 0; j < kWaves; ++j) {
-                    if (r < round0[j] || r >= round0[j + 1]) continue;
-                    if (w == wave) slot0 = run[j];
-                    run[j] += n;
+                for (int w = 0; w < kWaves; ++w) {
+                    const uint32_t r = batch + w;
+                    if (r < own0 || r >= own1) continue;
+                    const int t = w * 64 + lane;
+                    tot_emit += rs.d[0][t];
+                    tot_ll += rs.d[1][t];
+                    tot_de += rs.d[2][t];
+                    tot_clamp += rs.d[3][t];
+                    tot_drop += rs.d[4][t];
+                    tot_w += rs.f[0][t];
+                    more += rs.cnt[w];
                 }
+                run_base += (uint32_t)__builtin_amdgcn_readfirstlane((int)more);
+                if (lane == 0) D.run[wave] = run_base;
+                __syncthreads();
+            } else {
+                list_store(run_base);
+                list_dropped(run_base);
+                wave_lds_sync();       // the list is read
+                run_base += listed;
+                tot_emit += acc_emit;
+                tot_ll += acc_ll;
+                tot_de += acc_de;
+                tot_clamp += acc_clamp;
+                tot_drop += acc_drop;
+                tot_w += acc_w;
             }
-            list_store(slot0);
-            list_dropped(slot0);
-            rs.d[4][tid] = acc_drop;
-            __syncthreads();
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) {
-                const uint32_t r = batch + w;
-                uint32_t lo = 0, hi = 0;
-#pragma unroll
-                for (int j = 0; j < kWaves; ++j)
-                    if (j == wave) { lo = round0[j]; hi = round0[j + 1]; }
-                if (r < lo || r >= hi) continue;
-                const int t = w * 64 + lane;
-                tot_emit += rs.d[0][t];
-                tot_ll += rs.d[1][t];
-                tot_de += rs.d[2][t];
-                tot_clamp += rs.d[3][t];
-                tot_drop += rs.d[4][t];
-                tot_w += rs.f[0][t];
-            }
-            __syncthreads();
         } else if constexpr (kLdsAcc) {
             LedgerSmem &rs = sm.led;
             rs.d[0][tid] += acc_emit;
@@ -1052,13 +1099,6 @@ void push_emit_kernel(const StepArgs<R> a) {
             tot_w += acc_w;
         }
     }
-    if constexpr (kRag) {
-        run_base = 0;
-#pragma unroll
-        for (int j = 0; j < kWaves; ++j)
-            if (j == wave) run_base = run[j];
-    }
-
     if (have && lane == 0) cold_args<R>().seg_count[c] = run_base;
 
     // the wave's condition bits; they travel in the block's partial row to the
@@ -1981,7 +2021,7 @@ int launch_step(PARTS *parts, const sr_fields_f32 *fields, const sr_grid *grid, 
     // the field-box gather: FP32 path, 3D, uniform chunks, not the learned sampler
     constexpr bool kFloat = std::is_same<R, float>::value;
     const bool ragged = chunks->start != nullptr;
-    const bool dealt = n_chunks <= kDealtChunks;
+    const bool dealt = deal_rounds(parts->n, n_chunks, prm->n_samples);
     const bool box = prm->gather == SR_GATHER_BOX && dim == 3 && !ragged &&
                      prm->sampler != SR_SAMPLER_MLP;
 #define SR_LAUNCH(DIMV, KMV, SMP, FL, BX)                                                      \
