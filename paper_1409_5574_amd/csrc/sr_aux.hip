@@ -384,35 +384,45 @@ __global__ __launch_bounds__(256) void hist_reduce(const double *work, int nbloc
 // compute unit (each writes and the reduction reads a whole map).  Of 2^20 electrons with
 // 24 photons a chunk on 32 x 64 bins: 27.6 us with a lane a chunk, whose 24 dependent turns
 // ran on 64 blocks; 12.4 us so.
+//
+// A turn takes as long with two photons in a wave as with 64, so where there are many
+// chunks a wave first reads the counts of as many as it has to take (64 at most), and
+// takes them a lane each where they hold few: none more than `per` / 4 photons, which
+// bounds the turns, and at most half of them more than three, for the cache lines that
+// each lane reads alone.  2^22 electrons on 32 x 64 bins, photons in a chunk on average: 1/2
+// 11 us (17 with a lane a chunk always, 21 with sixteen always), 2 15 us (20, 25), 5 23
+// (35, 25), 10 23 (58, 25), 24 29 (120, 30).
+constexpr int64_t kAngularManyChunks = 8192;       // two turns
 constexpr int kMaxAngularBins = 4096;
 constexpr int kAngularBlocks = 256;
 constexpr int kAngularLanes = 16;
 constexpr int kAngularChunks = 256 / kAngularLanes;      // chunks of a block at a time
+template <bool MANY>
 __global__ __launch_bounds__(256) void angular_kernel(sr_photon_buf ph, const int64_t *start,
                                                       int64_t n_chunks, int64_t n, float3 ax,
                                                       float3 e1, float3 e2, int n_theta,
-                                                      int n_phi, double *work) {
+                                                      int n_phi, int per, double *work) {
     extern __shared__ double sh[];   // [n_theta * n_phi + 1]
     const int nvals = n_theta * n_phi + 1;
     for (int b = threadIdx.x; b < nvals; b += blockDim.x) sh[b] = 0.0;
     __syncthreads();
     const float t_scale = (float)n_theta * 0.63661977236758134f;   // n_theta / (pi/2)
     const float p_scale = (float)n_phi * 0.15915494309189535f;     // n_phi / (2 pi)
-    const int sub = threadIdx.x % kAngularLanes;
-    for (int64_t c = (int64_t)blockIdx.x * kAngularChunks + threadIdx.x / kAngularLanes; c < n_chunks;
-         c += (int64_t)gridDim.x * kAngularChunks) {
+    const auto segment = [&](int64_t c, int64_t &base) {      // first slot and photons held
         const int64_t s0 = start ? start[c] : c * (int64_t)kChunk;
         const int64_t e0 = start ? start[c + 1] : min(s0 + (int64_t)kChunk, n);
-        const int64_t cap = (e0 - s0) * ph.per_particle;
-        const int64_t cnt = min((int64_t)ph.seg_count[c], cap);
-        const int64_t base = s0 * ph.per_particle;
-        for (int64_t q0 = sub; q0 < cnt; q0 += 2 * kAngularLanes) {
+        base = s0 * ph.per_particle;
+        return min((int64_t)ph.seg_count[c], (e0 - s0) * ph.per_particle);
+    };
+    // photons base + first, base + first + step, ..., two at a time
+    const auto walk = [&](int64_t base, int64_t cnt, int first, int step) {
+        for (int64_t q0 = first; q0 < cnt; q0 += 2 * step) {
             float e[2], d[2][3];
             bool on[2];
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
-                on[j] = q0 + j * kAngularLanes < cnt;
-                const int64_t o = base + (on[j] ? q0 + j * kAngularLanes : q0);
+                on[j] = q0 + j * step < cnt;
+                const int64_t o = base + (on[j] ? q0 + j * step : q0);
                 e[j] = ph.eps[o] * ph.w[o];
                 for (int a = 0; a < 3; ++a) d[j][a] = ph.dir[a][o];
             }
@@ -432,6 +442,33 @@ __global__ __launch_bounds__(256) void angular_kernel(sr_photon_buf ph, const in
                 }
                 atomicAdd(&sh[bin], (double)e[j]);
             }
+        }
+    };
+    const int sub = threadIdx.x % kAngularLanes;
+    if (MANY) {
+        // a wave reads the counts of its next `per` chunks together: a lane each where they
+        // all hold a few
+        const int lane = threadIdx.x % 64;
+        for (int64_t r = ((int64_t)blockIdx.x * 4 + threadIdx.x / 64) * per; r < n_chunks;
+             r += (int64_t)gridDim.x * 4 * per) {
+            const int64_t end = min(r + per, n_chunks);
+            int64_t base = 0, cnt = 0;
+            if (r + lane < end) cnt = segment(r + lane, base);
+            if (__ballot(4 * cnt > per) == 0 && 2 * __popcll(__ballot(cnt > 3)) <= per) {
+                walk(base, cnt, 0, 1);
+            } else {
+                for (int64_t c = r + lane / kAngularLanes; c < end; c += 64 / kAngularLanes) {
+                    cnt = segment(c, base);
+                    walk(base, cnt, sub, kAngularLanes);
+                }
+            }
+        }
+    } else {
+        for (int64_t c = (int64_t)blockIdx.x * kAngularChunks + threadIdx.x / kAngularLanes; c < n_chunks;
+             c += (int64_t)gridDim.x * kAngularChunks) {
+            int64_t base;
+            const int64_t cnt = segment(c, base);
+            walk(base, cnt, sub, kAngularLanes);
         }
     }
     __syncthreads();
@@ -495,10 +532,17 @@ extern "C" int sr_angular_histogram(const sr_photon_buf *ph, const sr_chunking *
     const int64_t groups = (n_chunks + kAngularChunks - 1) / kAngularChunks;
     const int nb = (int)(groups < kAngularBlocks ? groups : kAngularBlocks);
     hipStream_t st = (hipStream_t)stream;
-    angular_kernel<<<nb, 256, sizeof(double) * nvals, st>>>(
-        *ph, chunks->start, n_chunks, n, make_float3((float)a[0], (float)a[1], (float)a[2]),
-        make_float3((float)u[0], (float)u[1], (float)u[2]),
-        make_float3((float)v[0], (float)v[1], (float)v[2]), n_theta, n_phi, work);
+    // chunks of a wave at a time, so that every wave has some
+    const int per = (int)std::min<int64_t>(64, (n_chunks + 4 * nb - 1) / (4 * nb));
+    const float3 av = make_float3((float)a[0], (float)a[1], (float)a[2]);
+    const float3 uv = make_float3((float)u[0], (float)u[1], (float)u[2]);
+    const float3 vv = make_float3((float)v[0], (float)v[1], (float)v[2]);
+    if (n_chunks > kAngularManyChunks)
+        angular_kernel<true><<<nb, 256, sizeof(double) * nvals, st>>>(*ph, chunks->start, n_chunks, n, av, uv,
+                                                                      vv, n_theta, n_phi, per, work);
+    else
+        angular_kernel<false><<<nb, 256, sizeof(double) * nvals, st>>>(*ph, chunks->start, n_chunks, n, av, uv,
+                                                                       vv, n_theta, n_phi, per, work);
     angular_reduce<<<(nvals + kAngularValues - 1) / kAngularValues, 256, 0, st>>>(work, nb, nvals, hist);
     SR_HIP_CHECK(hipGetLastError());
     return SR_OK;
