@@ -509,23 +509,27 @@ __global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))
 //
 // The box holds fixed-point integers, not floats: on gfx950 an LDS float
 // atomic add takes about 40 times as long as an integer one, and it was the
-// bulk of the deposit's time.  A particle's contributions are bounded: on
+// bulk of the deposit's time.  Each contribution v is rounded to an integer
+// multiple of 2^(e-21), where 2^e bounds every contribution of the block: on
 // each axis |v| <= |c_a| |du_a| (the partial sums of D over a hat shape are
 // bounded by the move du in cells, the transverse factor lies in [0, 1]), and
 // |v| <= |c_z| for the 2D Jz.  A node takes at most one contribution per
-// particle and component, so a node's sum is below the sum S of the bounds of the
-// particles of the slab.  With 2^e > S, each contribution is rounded to an integer
-// multiple of 2^(e-31): the sums stay below 2^31 (the bounds carry a margin of a
-// thousandth), and the integer adds are exact and independent of order.  The
-// rounding error per contribution is at most 2^(e-32) <= 2^-31 S.  That is absolute:
-// a node whose current is far below S in a block that also holds a much heavier or
-// faster particle keeps only that absolute accuracy.  So of a box taken in slabs the
-// particles whose bound is below 2^-12 S add to the grid directly, in 32 bits, as all
-// particles outside the window do.  Against 64 bits, rms error over rms current: 65 536
-// electrons on 64^3, 0.3 cells after their sort, 1.2e-6, 200 000 on 300^2 ten cells after
-// it 1.3e-6.  With units of 2^-21 of the block's largest bound, which takes 512
-// contributions of that size, it was 3.5e-6 and 2.1e-6; 2.1e-6 and 1.9e-6 with the
-// particles outside of one window added directly.
+// particle and component, so a sum stays below 512 * 2^21 = 2^30, and the
+// integer adds are exact and independent of order.  The rounding error per
+// contribution is at most half a unit, 2^(e-22) <= 2^-21 B with B the block's
+// largest bound, so a node's block sum is within n 2^-21 B <= 2^-12 B of the
+// exact sum of its n <= 512 contributions.  That bound is absolute: a node
+// whose current is far below B in a block that also holds a much heavier or
+// faster particle keeps only that absolute accuracy.
+//
+// The particles of a box taken in slabs would otherwise add to the grid in 32 bits, most
+// of them, and lose nothing by it here: a slab's unit is 2^(e-31) with 2^e above the sum
+// S of its particles' bounds, which is all that a node's sum can reach (the bounds carry a
+// margin of a thousandth), and particles whose bound is below 2^-12 S add to the grid
+// directly.  Against 64 bits, rms error over rms current, as so, with one window and direct
+// adds, and with the units of a box taken at once: 65 536 electrons on 64^3, 0.3 cells
+// after their sort, 1.2e-6, 2.1e-6, 3.5e-6; 200 000 on 300^2, ten cells after it, 1.3e-6,
+// 1.9e-6, 2.1e-6.
 //
 // 2^23 electrons, two a cell, in 4x4x4 tiles take 310 us right after the sort, where
 // the general stencil for all of them took 437; 380 us after 407 steps of a wake, 686
@@ -536,7 +540,11 @@ __global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))
 constexpr int kDepThreads = 512;   // particles per block
 constexpr int kDepCells = 3072;
 constexpr int kDepRows = kDepCells / 4;   // a box is at least 4 nodes wide
-constexpr int kDepBits = 31;              // S lies below 2^kDepBits units
+// 2^kDepFracBits units per bound and at most kDepThreads contributions per
+// node: sums stay below 2^30
+constexpr int kDepFracBits = 30 - 9;
+static_assert(kDepThreads == 512, "kDepFracBits assumes 2^9 particles per block");
+constexpr int kDepSumBits = 31;           // in slabs: S lies below 2^kDepSumBits units
 constexpr float kDepLight = 0x1p-12f;     // of S
 // Slabs are a chain: below 384 blocks two at most.  Sparse sets, one slab, two, eight: 5000
 // electrons at 0.03 per cell in 2D 15, 15, 39 us; 140 000 at 1/4 to 0.003 one against eight
@@ -758,10 +766,17 @@ __global__ __launch_bounds__(kDepThreads) __attribute__((amdgpu_waves_per_eu(6))
         return;                     // no live particle (the condition is block-wide)
     const float bnd = bx.bnd;
     if (!(bnd > 0.0f)) return;      // block-wide: every contribution is zero
-    // A bound that is not finite, or too large or too small for the sums and the scale
-    // to be finite floats, sends the whole block to the float path.
-    const bool fixed = bnd <= 1.0e35f && bnd >= 0x1p-90f;
+    // bnd < 2^e: contributions in units of 2^(e - kDepFracBits).  A
+    // non-finite bound, or one so small that 2^(kDepFracBits - e) would not
+    // be a finite float, sends the whole block to the float path; in slabs so does one
+    // whose sums or scale might not be.
+    int e = 0;
+    (void)frexpf(bnd, &e);
+    const bool fixed = bx.slabs == 1 ? bnd <= 3.0e38f && e >= -100 : e <= 115 && e >= -80;
     if (!fixed) bx.slabs = 1;
+    float to_fix = fixed ? ldexpf(1.0f, kDepFracBits - e) : 0.0f;
+    float from_fix = fixed ? ldexpf(1.0f, e - kDepFracBits) : 0.0f;
+    float least = 0.0f;
     const bool in_cell = m.live && fixed && stays<DIM>(m);
     for (int t = 0; t < bx.slabs; ++t) {
         DepBox w;
@@ -770,7 +785,7 @@ __global__ __launch_bounds__(kDepThreads) __attribute__((amdgpu_waves_per_eu(6))
         const int e0 = w.ext[0], e01 = w.ext[0] * w.ext[1];
         if (t) __syncthreads();        // the box is flushed, the list is read
         if (threadIdx.x == 0) listed = 0;
-        {
+        if (bx.slabs > 1) {
             const float b = wave_sum_f(m.live && mine ? m.bound : 0.0f);
             if ((threadIdx.x & 63) == 0) bsum[threadIdx.x >> 6] = b;
         }
@@ -779,19 +794,21 @@ __global__ __launch_bounds__(kDepThreads) __attribute__((amdgpu_waves_per_eu(6))
             box_rows<DIM>(row, w, G);
         }
         __syncthreads();
-        float sum_b = 0.0f;
+        if (bx.slabs > 1) {
+            float sum_b = 0.0f;
 #pragma unroll
-        for (int q = 0; q < kDepThreads / 64; ++q) sum_b += bsum[q];
-        int e = 0;
-        (void)frexpf(fmaxf(sum_b, 0x1p-90f), &e);
-        const float to_fix = fixed ? ldexpf(1.0f, kDepBits - e) : 0.0f;
-        const float from_fix = fixed ? ldexpf(1.0f, e - kDepBits) : 0.0f;
-        const float least = bx.slabs > 1 ? sum_b * kDepLight : 0.0f;
+            for (int q = 0; q < kDepThreads / 64; ++q) sum_b += bsum[q];
+            (void)frexpf(fmaxf(sum_b, 0x1p-82f), &e);
+            to_fix = ldexpf(1.0f, kDepSumBits - e);
+            from_fix = ldexpf(1.0f, e - kDepSumBits);
+            least = sum_b * kDepLight;
+        }
         bool now = in_cell && mine && m.bound >= least;
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
+            // (the general stencil's nodes, so that a window holds the same particles)
             const int b = U[a] - w.org[a];
-            now = now && b >= 0 && b + 1 <= w.ext[a] - 1;
+            now = now && b >= 0 && b + 2 <= w.ext[a] - 1;
         }
         if (now) {
             const int l0 = (U[0] - w.org[0]) + e0 * (U[1] - w.org[1]) +
