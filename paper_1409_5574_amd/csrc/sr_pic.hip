@@ -406,20 +406,20 @@ __device__ __forceinline__ void charge_direct(const int I[3], const float F[3], 
 
 // The direct adds alone, for what the box does not pay for: a box block is a chain of
 // some 3 us and 2 us a slab, and where few particles share a node it adds as often.
-// Box against direct, us, sorted and one cell of drift later (3D / 2D, electrons, per
-// cell): 12 000 at 2: 6.5 against 6.4; 80 000 at 1/2: 9 and 13 against 19 and 25 in 3D, 7.6
-// and 8.3 against 9.2 and 10.1 in 2D; 80 000 at 0.03: 24 and 35 against 28 and 31, and 22 and
-// 24 against 15 and 16; 20 000 at 0.06: 17 and 24 against 8 and 9, and 11 and 13 against 6.
+// Box against direct, us, right after the sort and one cell of drift later: 3D 12 000
+// electrons at 2 per cell 6.5 and 6.3 against 6.4 and 6.2; 40 000 at 1/4 10 and 14 against 12
+// and 14, at 0.06 14 and 19 against 13 and 15; 80 000 at 0.06 17 and 28 against 25 and 29; 2D
+// 80 000 at 1/2 7.6 and 8.3 against 9.2 and 10.1, at 0.06 14 and 21 against 13 and 14.
 // From 2^21 adds on a box is sought at any density (a set can be dense in a thin part of
 // its grid): 300 000 unsorted 120 against 118 us, sorted at 0.03 56 against 98.  Eight
-// slabs at that size: 1 M at 0.06 in 2D 68 us, 91 with up to two; below it four: 80 000 at
-// 1/2 three cells of drift after the sort 34 us, 43 with up to eight.
-constexpr int64_t kRhoAnyAdds = (int64_t)1 << 21, kRhoMinAdds = 196608;
-constexpr double kRhoMinPairs = 16384.0;      // n^2 / cells
+// slabs at that size: 1 M at 0.06 in 2D 68 us, 91 with up to two; below it four: 80 000 in
+// 3D at 1/2 three cells of drift after the sort 34 us, 43 with up to eight.
+constexpr int64_t kRhoAnyAdds = (int64_t)1 << 21, kRhoMinAdds = (int64_t)1 << 18;
+constexpr double kRhoMinShared = 40960.0;      // n adds / cells
 inline int rho_slabs(int64_t n, int dim, double cells) {      // 0: direct
     const int64_t adds = n << dim;
     if (adds >= kRhoAnyAdds) return kDepSlabs;
-    return adds >= kRhoMinAdds && (double)n * (double)n >= kRhoMinPairs * cells ? 4 : 0;
+    return adds >= kRhoMinAdds && (double)n * (double)adds >= kRhoMinShared * cells ? 4 : 0;
 }
 template <int DIM>
 __global__ __launch_bounds__(kRhoThreads) void rho_direct_kernel(sr_particles_f32 P, PicGrid G, float qv,
@@ -457,6 +457,7 @@ __global__ __launch_bounds__(kRhoThreads) __attribute__((amdgpu_waves_per_eu(5))
     if (active && !in_box && (qw != 0.0f || !fin))
         charge_direct<DIM>(I, F, qw, G, rho);
     if (!boxed) return;            // the condition is block-wide
+    __syncthreads();               // (not for the data: 263 us for the sort and deposit, 266 without)
     int e = 0;
     (void)frexpf(bx.bnd, &e);      // bnd < 2^e
     const double to_fix = ldexp(1.0, kRhoBits - e), from_fix = ldexp(1.0, e - kRhoBits);
@@ -546,11 +547,16 @@ constexpr int kDepFracBits = 30 - 9;
 static_assert(kDepThreads == 512, "kDepFracBits assumes 2^9 particles per block");
 constexpr int kDepSumBits = 31;           // in slabs: S lies below 2^kDepSumBits units
 constexpr float kDepLight = 0x1p-12f;     // of S
-// Slabs are a chain: below 384 blocks two at most.  Sparse sets, one slab, two, eight: 5000
-// electrons at 0.03 per cell in 2D 15, 15, 39 us; 140 000 at 1/4 to 0.003 one against eight
-// 1.11 times faster to 1.15 slower; 200 000, eight slabs 1.25 times faster than the direct
-// adds on average over densities and drifts, two 1.10.
-constexpr int64_t kDepSlabsFrom = 196608;
+// Slabs are a chain, so where the blocks do not fill the chip fewer are allowed.  Times with
+// direct adds over times with up to two, four and eight slabs, sets from two electrons per
+// cell to 0.003, at 0.3 to 10 cells after their sort, mean (worst): 3D 12 000 1.14 (1.04),
+// 1.13 (0.93), 1.03 (0.59); 40 000 1.07, 1.09, 1.07 (1.02 all three); 200 000 1.03, 1.07,
+// 1.13 (1.00).  2D 24 000 1.21 (1.08), 1.15 (0.95), 1.00 (0.62); 100 000 1.11, 1.15, 1.19
+// (1.03); 140 000 1.12 (1.01), 1.13 (0.91), 1.13 (0.87); 200 000 1.10, 1.18, 1.25 (1.01).
+inline int current_slabs(int64_t n, int dim) {
+    if (dim == 3) return n < 24576 ? 2 : n < 40960 ? 4 : kDepSlabs;
+    return n < 65536 ? 2 : n < 196608 ? 4 : kDepSlabs;
+}
 
 struct Move {
     int I[3];              // old cell of the particle on each axis
@@ -986,7 +992,7 @@ extern "C" int sr_deposit_current(const sr_particles_f32 *parts, const float *x_
     if (!parts->w || (dim == 2 && (!parts->p[0] || !parts->p[1] || !parts->p[2])))
         return SR_E_INVAL;
     const unsigned nb = (unsigned)((parts->n + kDepThreads - 1) / kDepThreads);
-    const int slabs = parts->n < kDepSlabsFrom ? 2 : kDepSlabs;
+    const int slabs = current_slabs(parts->n, dim);
     hipStream_t st = (hipStream_t)stream;
     if (dim == 3)
         current_kernel<3><<<nb, kDepThreads, 0, st>>>(*parts, x_old[0], x_old[1], x_old[2], G, (float)charge,

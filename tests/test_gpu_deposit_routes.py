@@ -23,14 +23,15 @@ def sr():
 
 
 @pytest.mark.parametrize("dim, n, count, weights, order", [
-    (3, (32, 32, 32), 24575, "wide", "sorted"),          # one add short of the box
-    (3, (32, 32, 32), 24577, "wide", "sorted"),
-    (3, (32, 32, 32), 24577, "equal", "unsorted"),       # no box: every block direct
-    (3, (48, 48, 48), 40000, "wide", "sorted"),          # sparse: direct
+    (3, (32, 32, 32), 32767, "wide", "sorted"),          # one electron short of the box
+    (3, (32, 32, 32), 32769, "wide", "sorted"),
+    (3, (32, 32, 32), 32769, "equal", "unsorted"),       # no box: every block direct
+    (3, (48, 48, 48), 40000, "wide", "sorted"),
+    (3, (128, 128, 96), 40000, "wide", "sorted"),        # sparse: direct
     (3, (256, 128, 64), 262144, "equal", "sorted"),      # sparse, and large enough to look
-    (2, (384, 384, 1), 49151, "zeros", "sorted"),
-    (2, (384, 384, 1), 49153, "zeros", "sorted"),
-    (2, (384, 384, 1), 49153, "wide", "unsorted"),
+    (2, (384, 384, 1), 65535, "zeros", "sorted"),
+    (2, (384, 384, 1), 65537, "zeros", "sorted"),
+    (2, (384, 384, 1), 65537, "wide", "unsorted"),
     (2, (5000, 3000, 1), 524288, "wide", "sorted"),
 ])
 def test_charge_on_both_sides_of_the_rule(sr, dim, n, count, weights, order):
@@ -51,8 +52,12 @@ def test_charge_on_both_sides_of_the_rule(sr, dim, n, count, weights, order):
 
 
 @pytest.mark.parametrize("dim, n, count, drift, heavy", [
-    (3, (256, 64, 4), 196607, 60.0, 1.0),       # two slabs at most: windows
-    (3, (256, 64, 4), 196609, 60.0, 1.0),       # up to eight
+    (3, (256, 64, 4), 24575, 60.0, 1.0),        # two slabs at most: windows
+    (3, (256, 64, 4), 40959, 20.0, 1.0),        # up to four
+    (3, (256, 64, 4), 40960, 60.0, 1.0),        # up to eight
+    (2, (2000, 64, 1), 65535, 300.0, 1.0),
+    (2, (2000, 64, 1), 196607, 90.0, 1.0),
+    (2, (2000, 64, 1), 196608, 300.0, 1.0),
     (3, (256, 64, 4), 200000, 60.0, 1e6),       # one heavy particle a block, and light ones
     (2, (2000, 64, 1), 200000, 300.0, 1e6),
 ])
