@@ -56,3 +56,22 @@ def test_gradient_sizes(sr, M):
     # 1024 rows at most are added one after another: 2^-24 of the largest partial sum each
     # in the worst case, their square root in the usual one; 4 times that, of the norm
     assert np.linalg.norm(g - parts) <= 4 * 32 * 2.0 ** -24 * np.linalg.norm(parts) + 1e-30
+
+
+@pytest.mark.parametrize("M", [1, 16, 63, 65, 129])
+def test_gradient_of_small_batches_matches_oracle(sr, M):
+    """Partial tiles and batches of a few waves against the FP64 gradient itself."""
+    print(f"[gpu-case] mlp gradient oracle {M}", flush=True)
+    flat, net = _net(sr, 13)
+    rng = np.random.default_rng(M + 2)
+    f = rng.uniform(-1.2, 1.2, (M, 2)).astype(np.float32)
+    d = rng.uniform(0.5, 1.0, M).astype(np.float32)
+    g = net.backward(torch.from_numpy(f).cuda(), torch.from_numpy(d).cuda()).cpu().numpy().astype(np.float64)
+    ref = omlp.backward(flat, f.astype(np.float64), d.astype(np.float64))
+    # a value that enters a product in bfloat16 is 2^-9 off; a gradient passes four such at
+    # most (dz3, dz2, an activation, dz1): 4 * 2^-9 of the largest of its array, 2.5 times
+    at = 0
+    for name, shape in omlp.SIZES:
+        k = int(np.prod(shape))
+        assert np.abs(g[at:at + k] - ref[at:at + k]).max() <= 2e-2 * np.abs(ref[at:at + k]).max() + 1e-12, name
+        at += k
