@@ -477,7 +477,8 @@ __device__ __forceinline__ bool load_field_box(const StepArgs<R> &a, BoxReduce &
 // the less of what they fetch is read again: at an eighth per cell, K = 1 and a sort every
 // ten steps 2054 us with six, 2039 with five.  The loop over a chunk's rounds with 4 to 8
 // trials sits a couple of VGPRs above the 96 that five waves allow; asking for five costs
-// no spills there.  Dealt rounds come to 111 and spill if asked for five.  The learned
+// no spills there.  Dealt rounds take 91 to 109 in 2D and, with all rows of a wave that
+// wraps in flight, 126 to 147 in 3D: up to four trials they are held to four waves.  The learned
 // sampler's come to 156 with 8 trials; four waves (128 VGPRs, and the 34 KB of LDS allow
 // four blocks per CU) took the step of 2^20 electrons from 159 to 152 us.
 template <typename R, int DIM, int KMAX, int SAMPLER, int MODE>
